@@ -26,6 +26,8 @@
 // 48-byte record and 16-byte conic, then every lane of the wave reads them as
 // LDS broadcasts.  No MFMA: per (pixel, entry) this is ~20 FP32 VALU
 // operations and one v_exp_f32.
+#include <type_traits>
+
 #include "block_scan.h"
 #include "common.h"
 
@@ -69,10 +71,12 @@ constexpr float kSkipMargin = 1.0f / 64.0f;
 // lets the backward skip an entry that no pixel of the tile can take without
 // changing any decision.
 // lamin = log2(alpha_min), or -inf when alpha_min = 0 (nothing skipped).
-__device__ __forceinline__ float4 stage_centre(const float4 r0, float o, float ox, float oy, float lamin) {
+// The last slot is the caller's.
+__device__ __forceinline__ float4 stage_centre(const float4 r0, float o, float ox, float oy, float lamin,
+                                               float last = 0.f) {
     const float cu = (r0.x - ox) + r0.z;
     const float cv = (r0.y - oy) + r0.w;
-    return make_float4(cu, cv, (lamin - __log2f(o)) - kSkipMargin, 0.f);
+    return make_float4(cu, cv, (lamin - __log2f(o)) - kSkipMargin, last);
 }
 
 // Sum over the 64 lanes of a wave: DPP within rows of 16, then 4 readlanes.
@@ -94,59 +98,74 @@ __device__ __forceinline__ float wave_sum(float v) {
             __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 63)));
 }
 
-// Value of the lane whose index differs from this lane's in bit log2(D) and
-// agrees in all lower bits (rotations within a row of 16 satisfy this for
-// D = 4 and D = 8; D >= 16 uses a full cross-lane permute).
+// Value of a lane whose index differs from this lane's in bit log2(D) and
+// agrees in all higher bits (the lower ones may differ: the fold below goes
+// from the high bits down, so they do not tell fields apart yet).
 template <int D>
 __device__ __forceinline__ float xchg(float x) {
+    static_assert(D < 16, "rows of 16 lanes");
     if constexpr (D == 1) return dpp_f32<0xb1>(x);          // quad_perm [1,0,3,2]
     else if constexpr (D == 2) return dpp_f32<0x4e>(x);     // quad_perm [2,3,0,1]
-    else if constexpr (D == 4) return dpp_f32<0x124>(x);    // row_ror:4
-    else if constexpr (D == 8) return dpp_f32<0x128>(x);    // row_ror:8
-    else return __shfl_xor(x, D, 64);
+    else if constexpr (D == 4) return dpp_f32<0x141>(x);    // row_half_mirror
+    else return dpp_f32<0x128>(x);                          // row_ror:8
 }
 
-// Reduce-scatter of NP per-lane fields by butterfly: at distance D each lane
-// keeps the half of its live fields selected by bit log2(D) of its lane index
-// and adds the partner's copy of that half.  NP - 1 exchanges instead of
-// NP * log2(64) for NP independent reductions.
-template <int NP, int D = 1>
-__device__ __forceinline__ void butterfly(float* v, int lane) {
-    if constexpr (D < NP) {
-        constexpr int H = NP / (2 * D);
+// Sum of a pair of fields over lane bit log2(D), each lane keeping one of
+// them: a where its bit is 0, b where it is 1.  Across rows the swap
+// instructions hand a's upper part against b's lower part, so the pair costs
+// one swap and one add and no selects (an LDS permute with selects, four
+// instructions and a round trip, before).  The two wait states before a swap
+// cover operands that vector instructions have just written, which the
+// compiler cannot see through the asm.
+template <int D>
+__device__ __forceinline__ float fold(float a, float b, int lane) {
+    if constexpr (D == 32) {
+        asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+        return a + b;
+    } else if constexpr (D == 16) {
+        asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+        return a + b;
+    } else {
         const bool hi = (lane & D) != 0;
-#pragma unroll
-        for (int i = 0; i < H; ++i) {
-            const float send = hi ? v[i] : v[i + H];
-            const float keep = hi ? v[i + H] : v[i];
-            v[i] = keep + xchg<D>(send);
-        }
-        butterfly<NP, 2 * D>(v, lane);
+        const float send = hi ? a : b, keep = hi ? b : a;
+        return keep + xchg<D>(send);
     }
 }
 
-template <int D>
-__device__ __forceinline__ float allreduce_from(float r) {
-    if constexpr (D < 64) return allreduce_from<2 * D>(r + xchg<D>(r));
-    else return r;
-}
-
-// Field whose wave total lane `lane` holds after wave_reduce_fields<NP>.
-template <int NP>
-__host__ __device__ constexpr int field_of_lane(int lane) {
-    int f = 0;
+// Reduce-scatter of N per-lane fields over the 64 lanes, one lane bit a
+// level: pairs of fields fold into one register; the odd one is summed into
+// both halves.  About 2 N instructions instead of 12 N for N reductions.
+template <int N, int D = 32>
+__device__ __forceinline__ float wave_reduce_fields(float (&v)[N], int lane) {
+    if constexpr (D == 0) {
+        static_assert(N == 1, "at most 64 fields");
+        return v[0];
+    } else {
+        constexpr int H = (N + 1) / 2;
+        float r[H];
 #pragma unroll
-    for (int D = 1; D < NP; D *= 2)
-        if (lane & D) f += NP / (2 * D);
-    return f;
+        for (int i = 0; i < N / 2; ++i) r[i] = fold<D>(v[2 * i], v[2 * i + 1], lane);
+        if constexpr (N % 2 != 0) {
+            if constexpr (D >= 16) r[H - 1] = fold<D>(v[N - 1], v[N - 1], lane);
+            else r[H - 1] = v[N - 1] + xchg<D>(v[N - 1]);
+        }
+        return wave_reduce_fields<H, D / 2>(r, lane);
+    }
 }
 
-// Sums v[0..NP) over the 64 lanes; returns, in every lane, the total of
-// field field_of_lane<NP>(lane).
-template <int NP>
-__device__ __forceinline__ float wave_reduce_fields(float (&v)[NP], int lane) {
-    butterfly<NP>(v, lane);
-    return allreduce_from<NP>(v[0]);
+// Field whose wave total this lane holds after wave_reduce_fields<N>, or -1
+// if a lower lane holds the same one.
+template <int N, int D = 32>
+__device__ __forceinline__ int field_of_lane(int lane) {
+    if constexpr (D == 0) {
+        return 0;
+    } else {
+        const int r = field_of_lane<(N + 1) / 2, D / 2>(lane);
+        const int bit = (lane & D) != 0 ? 1 : 0;
+        if (r < 0) return -1;
+        if (2 * r + 1 < N) return 2 * r + bit;
+        return bit ? -1 : 2 * r;
+    }
 }
 
 template <int TW, int TH, int NF>
@@ -346,9 +365,6 @@ __global__ void __launch_bounds__(64) k_composite_bwd(
     constexpr int SS4 = staged_float4s(NF);
     constexpr int GS = grad_floats(NF);
     constexpr int NG = 10 + 2 * NF;            // gradient fields per entry
-    constexpr int NGP = NG <= 16 ? 16 : 32;    // padded to a power of two
-    static_assert(field_of_lane<NGP>(0) == 0 && field_of_lane<NGP>(NGP / 2) == 1,
-                  "lanes 0 and NGP / 2 hold the totals of fields 0 and 1");
     __shared__ float4 srec[SS4][B];
     __shared__ uint32_t sitem[B];
 
@@ -425,7 +441,11 @@ __global__ void __launch_bounds__(64) k_composite_bwd(
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) maxl = max(maxl, (uint32_t)__shfl_xor((int)maxl, o, 64));
+    // the record field this lane adds to, and its constant factor: the exponent
+    // is in log2 units, and the centre's terms lack -2
+    const int fld = field_of_lane<NG>(lane);
     const float LN2 = 0.6931471805599453f;
+    const float fscale = fld == 0 || fld == 1 ? -2.0f * LN2 : fld < 5 ? LN2 : 1.0f;
 
     for (uint32_t hi = min(rg.x + maxl, rg.y); hi > rg.x; ) {
         const uint32_t lo = (hi - rg.x > (uint32_t)B) ? hi - B : rg.x;
@@ -436,25 +456,30 @@ __global__ void __launch_bounds__(64) k_composite_bwd(
             sitem[lane] = item;
             const float4* r = rec + (size_t)item * RS4;
             const float4 r1 = conic[item];
-            srec[0][lane] = stage_centre(r[0], r1.w, ox, oy, lamin);
+            // 1 / o turns sum gq into d/do (0 where o is too small for either)
+            srec[0][lane] = stage_centre(r[0], r1.w, ox, oy, lamin, r1.w > 1e-30f ? 1.0f / r1.w : 0.f);
             srec[1][lane] = r1;
 #pragma unroll
             for (int q = 1; q < RS4; ++q) srec[q + 1][lane] = r[q];
         }
         __syncthreads();
+        // the centre and conic of the next entry are read while this one is
+        // taken (a wave alone on its SIMD otherwise waits for LDS each time)
+        float4 cn = srec[0][0], r1n = srec[1][0];
         for (int s = 0; s < cnt; ++s) {
             const uint32_t kidx = hi - 1 - (uint32_t)s - rg.x;   // position in the tile list
-            const float4 c = srec[0][s], r1 = srec[1][s];
+            const float4 c = cn, r1 = r1n;
+            cn = srec[0][(s + 1) & (B - 1)];
+            r1n = srec[1][(s + 1) & (B - 1)];
             // phase 1: which pixels can composite this entry (the forward's
             // decisions: not past the pixel's last entry, exponent above the
             // certain-skip threshold); an entry no pixel takes costs no more
-            float dx[PPT], dy[PPT], qe[PPT];
+            float dy[PPT], qe[PPT];
             bool pass[PPT];
             bool anyp = false;
             const SplatCol col = splat_col(c, r1, fpx[0]);   // the lane's pixels share a column
 #pragma unroll
             for (int i = 0; i < PPT; ++i) {
-                dx[i] = col.dx;
                 qe[i] = splat_row(col, c, r1, fpy[i], dy[i]);
                 pass[i] = kidx < last[i] && !(qe[i] < c.z);
                 anyp |= pass[i];
@@ -470,81 +495,77 @@ __global__ void __launch_bounds__(64) k_composite_bwd(
             }
             // Sums start from their first term (pixel 0), not from 0 + term:
             // the compiler must keep an addition of +0 (it turns -0 into +0)
-            float g[NGP];
-#pragma unroll
-            for (int q = NG; q < NGP; ++q) g[q] = 0.f;
+            float g[NG];
             auto put = [](float& acc, float term, int i) { acc = i == 0 ? term : acc + term; };
             bool any = false;
             // Branch-free per pixel: inactive pixels contribute zero and keep
             // their state (selects instead of divergent blocks, so the field
             // registers are never copied at control-flow joins).
-            // The conic and centre gradients only need, per lane (one pixel
-            // column, so one dx), sum gq, sum gq dy and sum gq dy^2
+            // The conic, centre and opacity gradients only need, per lane (one
+            // pixel column, so one dx), sum gq, sum gq dy and sum gq dy^2, with
+            // gq = dL/dq / ln 2 = o G dL/dalpha
             float p0, p1, p2;
+            // alpha = o 2^q unless clamped at alpha_max, where it has no
+            // gradient; an entry with o <= alpha_max never is (2^q <= 1 but for
+            // the rounding of q, which the margin covers)
+            auto pixels = [&](auto clamps) {
 #pragma unroll
-            for (int i = 0; i < PPT; ++i) {
-                const float G = __builtin_amdgcn_exp2f(qe[i]);
-                const float oG = r1.w * G;
-                const float a = fminf(oG, amax);
-                const bool act = pass[i] && a >= amin;
-                any |= act;
-                // ae = alpha of a composited entry, 0 otherwise: with ae = 0
-                // every state update below is the identity (rcp(1) = 1)
-                const float ae = act ? a : 0.0f;
-                const float rom = __builtin_amdgcn_rcpf(1.0f - ae);
-                const float Ti = T[i] * rom;
-                const float T2 = Ti * Ti;
-                const float u = gr[i][0] * r2.x + gr[i][1] * r2.y + gr[i][2] * r2.z + gd[i] * r2.w;
-                float v = gS[i][0] * as[0] + gC[i][0] * ac[0];
+                for (int i = 0; i < PPT; ++i) {
+                    const float oG = r1.w * __builtin_amdgcn_exp2f(qe[i]);
+                    const float a = decltype(clamps)::value ? fminf(oG, amax) : oG;
+                    const bool act = pass[i] && a >= amin;
+                    any |= act;
+                    // ae = alpha of a composited entry, 0 otherwise: with ae = 0
+                    // every state update below is the identity (rcp(1) = 1)
+                    const float ae = act ? a : 0.0f;
+                    const float rom = __builtin_amdgcn_rcpf(1.0f - ae);
+                    const float Ti = T[i] * rom;
+                    const float u = gr[i][0] * r2.x + gr[i][1] * r2.y + gr[i][2] * r2.z + gd[i] * r2.w;
+                    float v = gS[i][0] * as[0] + gC[i][0] * ac[0];
 #pragma unroll
-                for (int k = 1; k < NF; ++k) v += gS[i][k] * as[k] + gC[i][k] * ac[k];
-                const float dA = Ti * u + T2 * v - rom * A[i];
-                T[i] = Ti;
-                const float w1 = ae * Ti;
-                const float w2 = ae * T2;
-                A[i] += w1 * u + w2 * (2.0f * v);
-                put(g[6], w1 * gr[i][0], i);
-                put(g[7], w1 * gr[i][1], i);
-                put(g[8], w1 * gr[i][2], i);
-                put(g[9], w1 * gd[i], i);
+                    for (int k = 1; k < NF; ++k) v += gS[i][k] * as[k] + gC[i][k] * ac[k];
+                    const float x = Ti * v, y = u + x;
+                    const float dA = Ti * y - rom * A[i];
+                    T[i] = Ti;
+                    const float w1 = ae * Ti;
+                    const float w2 = w1 * Ti;
+                    A[i] += w1 * (y + x);
+                    put(g[6], w1 * gr[i][0], i);
+                    put(g[7], w1 * gr[i][1], i);
+                    put(g[8], w1 * gr[i][2], i);
+                    put(g[9], w1 * gd[i], i);
 #pragma unroll
-                for (int k = 0; k < NF; ++k) {
-                    put(g[10 + 2 * k], w2 * gS[i][k], i);
-                    put(g[11 + 2 * k], w2 * gC[i][k], i);
+                    for (int k = 0; k < NF; ++k) {
+                        put(g[10 + 2 * k], w2 * gS[i][k], i);
+                        put(g[11 + 2 * k], w2 * gC[i][k], i);
+                    }
+                    const float aq = decltype(clamps)::value && oG > amax ? 0.0f : ae;
+                    const float gq = dA * aq;
+                    const float gy = gq * dy[i];
+                    put(p0, gq, i);
+                    put(p1, gy, i);
+                    put(p2, gy * dy[i], i);
                 }
-                // alpha = o 2^q unless clamped (then alpha has no gradient);
-                // gq = dL/dq / ln 2
-                const float dAe = (act && oG <= amax) ? dA : 0.0f;
-                const float gq = dAe * a;
-                put(g[5], G * dAe, i);                           // d/do
-                const float gy = gq * dy[i];
-                put(p0, gq, i);
-                put(p1, gy, i);
-                put(p2, gy * dy[i], i);
-            }
-            {
-                const float dxl = dx[0];                         // the lane's column
-                g[0] = dxl * p0;                                 // sum gx
-                g[1] = p1;                                       // sum gy
-                g[2] = (dxl * dxl) * p0;                         // d/dcA
-                g[3] = dxl * p1;                                 // d/dcB
-                g[4] = p2;                                       // d/dcC
-            }
+            };
+            if (__builtin_amdgcn_readfirstlane((int)(r1.w > 0.9999f * amax)))
+                pixels(std::true_type{});
+            else
+                pixels(std::false_type{});
             if (__ballot(any) == 0ull) continue;
+            {
+                const float gx = col.dx * p0;                    // sum gx; sum gy = p1
+                const float hb = 0.5f * r1.y;
+                g[0] = r1.x * gx + hb * p1;                      // d/du: -(2 cA sum gx + cB sum gy)
+                g[1] = r1.z * p1 + hb * gx;                      // d/dv: -(2 cC sum gy + cB sum gx)
+                g[2] = col.dx * gx;                              // d/dcA
+                g[3] = col.dx * p1;                              // d/dcB
+                g[4] = p2;                                       // d/dcC
+                g[5] = p0;                                       // d/do o
+            }
             // one reduce-scatter over the wave, then one atomic instruction whose
             // lanes add consecutive fields of the entry's gradient record
-            float tot = wave_reduce_fields<NGP>(g, lane);
-            const int fld = field_of_lane<NGP>(lane);
-            // fields 0 and 1 hold sum gx and sum gy (lanes 0 and NGP / 2):
-            // d/du = -(2 cA sum gx + cB sum gy), d/dv = -(2 cC sum gy + cB sum gx)
-            const float sgx = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, tot), 0));
-            const float sgy =
-                __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, tot), NGP / 2));
-            if (fld == 0) tot = -(2.0f * r1.x * sgx + r1.y * sgy);
-            if (fld == 1) tot = -(2.0f * r1.z * sgy + r1.y * sgx);
-            if (fld < 5) tot *= LN2;
-            if (lane < NGP && fld < NG && tot != 0.f)
-                atomicAdd(grec + (size_t)sitem[s] * GS + fld, tot);
+            const float tot = wave_reduce_fields<NG>(g, lane) * (fld == 5 ? c.w : fscale);
+            if (fld >= 0 && tot != 0.f) atomicAdd(grec + (size_t)sitem[s] * GS + fld, tot);
         }
         hi = lo;
     }
