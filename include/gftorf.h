@@ -197,9 +197,10 @@ size_t gftorf_workspace_size(int64_t n, int32_t n_frames, const gftorf_config* c
  * (paper §3 Eqs. 2, 4, 5; every frame carries its own time, so raw quads
  * of a dynamic scene can be rendered at the instants they were captured).
  * Stages: per (frame, Gaussian) projection and tile rectangle -> stable
- * frame-major depth sort of the items -> per-tile Gaussian lists built in
- * depth order (chunk counts, column scan, ordered placement) -> front-to-back
- * compositing, one workgroup per (frame, tile).
+ * frame-major depth sort of the items -> Gaussian lists of groups of 8x8
+ * tiles in depth order (chunk counts, column scan, ordered placement) and the
+ * length of every tile's list -> front-to-back compositing, one workgroup per
+ * (frame, tile), which filters its tile's list out of its group's.
  * The workspace `ws` keeps the sorted lists and per-Gaussian records that
  * gftorf_render_bwd needs: pass the same ws, untouched, to the backward.
  * If the pair count exceeds cfg->max_pairs the outputs are invalid and
@@ -253,7 +254,8 @@ int gftorf_clear_status(void* ws, void* stream);
  *   tile_ranges: [n_frames * n_tiles][2] [start, end) of every tile list in
  *     the pair arrays.
  * Every destination may be NULL.  Synchronises `stream` to read the pair
- * count. */
+ * count.  The forward keeps of every tile list the part that it composited;
+ * with pair_item this call completes the lists in the workspace first. */
 int gftorf_copy_lists(const void* ws, int64_t n, int32_t n_frames, const gftorf_config* cfg,
                       uint32_t* pair_key, uint32_t* pair_item, int64_t pair_capacity,
                       uint32_t* depth_key, uint32_t* depth_item, uint32_t* item_count,

@@ -326,6 +326,10 @@ int gftorf_copy_lists(const void* ws, int64_t n, int32_t n_frames, const gftorf_
         gft::launch_keys_from_ranges(P, w, pair_key, np, s);
         e = hipGetLastError();
     }
+    if (pair_item && np && e == hipSuccess) {   // the forward writes the composited part of each list only
+        gft::launch_tile_lists(P, w, s);
+        e = hipGetLastError();
+    }
     cp(pair_item, w.tval, 4 * np);
     cp(depth_key, w.dkey[db], 4 * (size_t)w.M);
     cp(depth_item, w.dval[db], 4 * (size_t)w.M);

@@ -35,9 +35,8 @@ struct BinGeom {
     int C;                 // items per level-A chunk
     int QC;                // chunks per frame
     int ng;                // groups of 8x8 tiles per frame
-    int S;                 // group-list entries per level-B segment
-    int R;                 // segments per placement chunk (R * S entries)
-    int64_t max_segments;  // bound on the level-B segments
+    int S;                 // group-list entries per counting segment
+    int64_t max_segments;  // bound on the counting segments
 };
 BinGeom bin_geometry(int64_t n, int32_t n_frames, int ntx, int nty, uint64_t cap);
 
@@ -110,15 +109,12 @@ struct Workspace {
     uint32_t* cntA;         // [F][QC][ng] per-chunk group counts, then column prefixes
     uint32_t* lenA;         // [F * ng] group-list lengths
     uint2* granges;         // [F * ng] group-list ranges in gval
-    uint32_t* seg_start;    // [F * ng + 1] first level-B segment of each group
-    uint32_t* chunk_start;  // [F * ng + 1] first placement chunk (R segments) of each group
-    uint4* chunk_info;      // [max chunks] per placement chunk: group, first and end entry, first segment
+    uint32_t* seg_start;    // [F * ng + 1] first counting segment of each group
     uint32_t* gval;         // [cap] item ids of the group lists
-    uint16_t* gloc;         // [cap] their rectangles clipped to the group, 3 bits per bound
-    uint32_t* cntB;         // [max_segments][64] per-segment tile counts, then prefixes
+    uint16_t* gloc;         // [cap] their rectangles clipped to the group (pack_rect)
     uint32_t* tcount;       // [F * n_tiles] pairs per (frame, tile)
     uint2* ranges;          // [F * n_tiles] [start, end) of each tile list in tval
-    uint32_t* tval;         // [cap] item ids of the tile lists
+    uint32_t* tval;         // [cap] item ids of the tile lists, each up to what the forward composited of it
     uint2* wcount;          // [F * n_tiles] forward (evaluations, composited) per work item
     float* grec;            // [M][grad_floats]
     int64_t M;
@@ -163,11 +159,8 @@ inline Workspace carve(void* base, int64_t n, int32_t F, int nf, int ntx, int nt
     w.lenA = reinterpret_cast<uint32_t*>(take(4 * KG));
     w.granges = reinterpret_cast<uint2*>(take(sizeof(uint2) * KG));
     w.seg_start = reinterpret_cast<uint32_t*>(take(4 * (KG + 1)));
-    w.chunk_start = reinterpret_cast<uint32_t*>(take(4 * (KG + 1)));
-    w.chunk_info = reinterpret_cast<uint4*>(take(sizeof(uint4) * (size_t)((g.max_segments + g.R - 1) / g.R + KG)));
     w.gval = reinterpret_cast<uint32_t*>(take(4 * cap));
     w.gloc = reinterpret_cast<uint16_t*>(take(2 * cap));
-    w.cntB = reinterpret_cast<uint32_t*>(take(4 * 64 * (size_t)g.max_segments));
     w.tcount = reinterpret_cast<uint32_t*>(take(4 * K));
     w.ranges = reinterpret_cast<uint2*>(take(sizeof(uint2) * K));
     w.tval = reinterpret_cast<uint32_t*>(take(4 * cap));
@@ -213,6 +206,7 @@ inline bool one_sweep_sort(const Params& P, const Workspace& w) {
 }
 hipError_t launch_binning(const Params& P, const Workspace& w, int dbuf, hipStream_t s);
 void launch_item_rects(const Workspace& w, int dbuf, uint2* out, hipStream_t s);
+void launch_tile_lists(const Params& P, const Workspace& w, hipStream_t s);   // completes every tile list
 void launch_keys_from_ranges(const Params& P, const Workspace& w, uint32_t* keys,
                              unsigned long long limit, hipStream_t s);
 hipError_t launch_composite_fwd(const Params& P, const gftorf_frame* frames, const Workspace& w,

@@ -29,6 +29,7 @@
 
 #include "block_scan.h"
 #include "common.h"
+#include "walk.h"
 
 namespace gft {
 
@@ -77,11 +78,6 @@ __device__ __forceinline__ float4 stage_centre(const float4 r0, float o, float o
     const float cv = (r0.y - oy) + r0.w;
     return make_float4(cu, cv, (lamin - __log2f(o)) - kSkipMargin, last);
 }
-
-// Lane masks held in scalar registers: the lanes whose condition (one
-// comparison, which then writes the mask itself) is true, and back.
-__device__ __forceinline__ uint64_t lanes(bool c) { return __builtin_amdgcn_ballot_w64(c); }
-__device__ __forceinline__ bool lane_of(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 
 // Sum over the 64 lanes of a wave: DPP within rows of 16, then 4 readlanes.
 template <int CTRL>
@@ -237,7 +233,10 @@ __device__ __forceinline__ void write_pixel(const Params& P, const gftorf_frame&
 template <int TW, int TH, int NF, int WPT, int U>
 __global__ void __launch_bounds__(64 * WPT) k_composite_fwd(Params P, const gftorf_frame* __restrict__ frames,
                                                             const uint2* __restrict__ ranges,
-                                                            const uint32_t* __restrict__ tval,
+                                                            const uint2* __restrict__ granges,
+                                                            const uint32_t* __restrict__ gval,
+                                                            const uint16_t* __restrict__ gloc,
+                                                            uint32_t* __restrict__ tval,
                                                             const float4* __restrict__ rec,
                                                             const float4* __restrict__ conic,
                                                             gftorf_outputs out, uint2* __restrict__ wcount) {
@@ -245,9 +244,17 @@ __global__ void __launch_bounds__(64 * WPT) k_composite_fwd(Params P, const gfto
     static_assert(PPT * 64 * WPT == TW * TH && 64 % U == 0, "whole waves and groups of entries");
     constexpr int RS4 = record_float4s(NF);
     constexpr int SS4 = staged_float4s(NF);
-    // each wave stages 64 list entries at a time into its own slice: most
-    // pixels stop after 100-200 entries, so short batches waste few loads
-    __shared__ float4 srec_w[WPT][SS4][64];
+    // 64 list entries are staged at a time (most pixels stop after 100-200, so
+    // short batches waste few loads).  SHARED: the workgroup's waves find and
+    // stage them together; otherwise each for itself, in its own slice.
+    constexpr bool SHARED = WPT == 4;
+    constexpr int NQ = SHARED ? 1 : WPT;
+    __shared__ float4 srec_w[NQ][SS4][64];
+    // group-list entries of the tile found but not yet staged: fewer than a
+    // batch, and one round of the walk more
+    constexpr uint32_t QN = SHARED ? 2048 : 512;
+    __shared__ uint32_t queue_w[NQ][QN];
+    __shared__ uint32_t found_w[2][WPT], going_w[2][WPT];   // SHARED: per wave, by turn
 
     const int w = xcd_remap(blockIdx.x, gridDim.x);
     const int f = w / P.n_tiles;
@@ -284,28 +291,83 @@ __global__ void __launch_bounds__(64 * WPT) k_composite_fwd(Params P, const gfto
     // stops at entry e has evaluated e of them, one that never stops all
     uint32_t n_eval = 0, n_comp = 0;
 
-    float4 (*srec)[64] = srec_w[sub];
-    for (uint32_t b0 = rg.x; b0 < rg.y && any != 0ull; b0 += 64) {
-        const uint32_t j = b0 + lane;
-        // the previous batch's LDS reads of every lane precede these writes
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        if (j < rg.y) {
-            const uint32_t item = tval[j];
-            const float4* r = rec + (size_t)item * RS4;
-            const float4 r0 = r[0];
-            srec[0][lane] = make_float4((r0.x - ox) + r0.z, (r0.y - oy) + r0.w, 0.f, 0.f);
-            srec[1][lane] = conic[item];
-#pragma unroll
-            for (int q = 1; q < RS4; ++q) srec[q + 1][lane] = r[q];
-        } else {   // past the end: alpha = -1, below every threshold
-            srec[0][lane] = make_float4(0.f, 0.f, 0.f, 0.f);
-            srec[1][lane] = make_float4(0.f, 0.f, 0.f, -1.f);
+    float4 (*srec)[64] = srec_w[SHARED ? 0 : sub];
+    uint32_t* queue = queue_w[SHARED ? 0 : sub];
+    auto sync = [] {   // LDS writes before this, reads after it, and the other way round
+        if constexpr (SHARED) {
+            __syncthreads();
+        } else {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        const int cnt = __builtin_amdgcn_readfirstlane((int)min(64u, rg.y - b0));
-        const uint32_t pos0 = b0 - rg.x + 1u;   // list position of the batch's first entry
+    };
+    const uint32_t len = (uint32_t)__builtin_amdgcn_readfirstlane((int)(rg.y - rg.x));
+    constexpr int NW = SHARED ? WPT : 1;
+    TileWalk<NW> walk = tile_walk<NW>(P, f, tx, ty, granges, gloc, SHARED ? sub : 0, lane);
+    uint32_t head = 0, queued = 0;   // of the queue
+    uint32_t item = 0;               // this lane's of the next batch
+    int turn = 0;
+    auto next_items = [&] {
+        while (queued < 64u && walk.more()) {
+            const typename TileWalk<NW>::Hits h = walk.round();
+            uint32_t tail = head + queued, all = h.count();
+            if constexpr (SHARED) {
+                if (lane == 0) found_w[turn][sub] = all;
+                __syncthreads();
+                all = 0;
+#pragma unroll
+                for (int q = 0; q < WPT; ++q) {
+                    const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)found_w[turn][q]);
+                    tail += q < sub ? n : 0u;
+                    all += n;
+                }
+                turn ^= 1;
+            }
+            h.each([&](uint32_t entry, uint32_t q) { queue[(tail + q) % QN] = entry; });
+            queued += all;
+        }
+        sync();
+        if (lane < (int)queued) item = gval[queue[(head + lane) % QN]];
+    };
+    if (len != 0u) next_items();
+    // some pixel of the wave (SHARED: of the tile, which has one inside the
+    // image; its waves pass the same barriers, also one with no pixel inside)
+    // has not stopped
+    bool going = SHARED || any != 0ull;
+    int cnt;
+    for (uint32_t pos = 0; pos < len && going; pos += (uint32_t)cnt) {
+        cnt = __builtin_amdgcn_readfirstlane((int)min(min(queued, 64u), len - pos));
+        if (cnt == 0) break;   // the list is cut at the pair capacity
+        sync();
+        {   // stage; past the end: alpha = -1, below every threshold
+            const bool have = lane < cnt;
+            if (have && (!SHARED || sub == 0))
+                tval[rg.x + pos + lane] = item;   // the backward walks the part that was composited
+            const float4* r = rec + (size_t)item * RS4;
+#pragma unroll
+            for (int q = 0; q < SS4; ++q) {   // SHARED: a slot per wave
+                if (SHARED && q % WPT != sub) continue;
+                if (q == 0) {
+                    float4 c = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (have) {
+                        const float4 r0 = r[0];
+                        c = make_float4((r0.x - ox) + r0.z, (r0.y - oy) + r0.w, 0.f, 0.f);
+                    }
+                    srec[0][lane] = c;
+                } else if (q == 1) {
+                    srec[1][lane] = have ? conic[item] : make_float4(0.f, 0.f, 0.f, -1.f);
+                } else if (have) {
+                    srec[q][lane] = r[q - 1];
+                }
+            }
+        }
+        sync();
+        head = (head + (uint32_t)cnt) % QN;
+        queued -= (uint32_t)cnt;
+        // the next batch's entries are found, and their items loaded, while
+        // this one is walked
+        next_items();
+        const uint32_t pos0 = pos + 1u;   // list position of the batch's first entry
         for (int k0 = 0; k0 < cnt && any != 0ull; k0 += U) {
             float a[U][PPT];
             float4 fld[U][SS4 - 2];
@@ -361,6 +423,16 @@ __global__ void __launch_bounds__(64 * WPT) k_composite_fwd(Params P, const gfto
                         last[i] = pos0 + (uint32_t)(k0 + u);
                     }
                 }
+        }
+        going = any != 0ull;
+        if constexpr (SHARED) {
+            const int t = (int)(pos / 64u) & 1;
+            if (lane == 0) going_w[t][sub] = going ? 1u : 0u;
+            __syncthreads();
+            uint32_t n = 0;
+#pragma unroll
+            for (int q = 0; q < WPT; ++q) n |= going_w[t][q];
+            going = __builtin_amdgcn_readfirstlane((int)n) != 0;
         }
     }
 #pragma unroll
@@ -637,7 +709,7 @@ hipError_t fwd_wpt(const Params& P, const gftorf_frame* frames, const Workspace&
     const unsigned blocks = (unsigned)(P.F * P.n_tiles);
 #define GFT_FWD(NF_)                                                                                          \
     hipLaunchKernelGGL((k_composite_fwd<TW, TH, NF_, WPT, U>), dim3(blocks), dim3(64 * WPT), 0, s, P, frames, \
-                       w.ranges, w.tval, w.rec, w.conic, out, w.wcount)
+                       w.ranges, w.granges, w.gval, w.gloc, w.tval, w.rec, w.conic, out, w.wcount)
     switch (P.nf) {
         case 1: GFT_FWD(1); break;
         case 2: GFT_FWD(2); break;

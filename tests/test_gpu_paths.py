@@ -1,0 +1,72 @@
+"""Edges of the kernels' own splits: rounds of the tile walk, groups cut by the
+image, tiles with pixels outside, and the introspection call between a forward
+and its backward."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+import scenes
+from gpu_common import GRAD_RTOL, assert_grads_close, assert_images_close, gpu_lists, mask_upstream, run_gpu
+from oracle import binning as obin
+from oracle import render as oref
+from paper_2505_05356_amd import raster
+
+pytestmark = pytest.mark.gpu
+
+
+# 256 group-list entries a round: lists of fewer, of one more, and of several
+# rounds; images whose last tiles and groups are cut, in every tile shape
+@pytest.mark.parametrize("n,width,height,tile", [
+    (3, 17, 9, (8, 8)), (255, 70, 66, (8, 8)), (257, 70, 66, (16, 16)), (1500, 129, 33, (16, 16)),
+    (1500, 257, 65, (32, 8)), (2100, 131, 130, (8, 8))])
+def test_tile_walk_edges(n, width, height, tile):
+    wl = scenes.tiny_scene(n, width, height, seed=n, log_scale_mean=float(np.log(0.05)))
+    cfg = dataclasses.replace(wl.cfg, tile_w=tile[0], tile_h=tile[1])
+    up = scenes.upstream_grads(1, cfg, seed=5)
+    ref = oref.render(wl.gaussians, wl.frames, cfg)
+    ok = ~ref["flagged"]
+    up = mask_upstream(up, ok)
+    gref = oref.render(wl.gaussians, wl.frames, cfg, upstream=up)["grads"]
+    res = run_gpu(wl.gaussians, wl.frames, cfg, upstream=up)
+    for k in ("rgb", "quad", "depth"):
+        assert_images_close(res[k], ref[k], ok, k)
+    for k in ("mean", "scale", "quat", "opacity_logit", "rgb", "albedo"):
+        assert_grads_close(res["grads"][k], gref[k], k)
+    # the lists are completed by the introspection call and equal the oracle's;
+    # a backward after it gives what the one before it gave
+    lists = gpu_lists(res, wl.gaussians, wl.frames, cfg)
+    pairs = obin.sorted_pairs(wl.gaussians, wl.frames, cfg)
+    assert np.array_equal(lists["pair_item"], pairs["index"].astype(np.uint32))
+    d = {k: torch.from_numpy(up[k]).cuda() for k in up}
+    again = raster.backward(res["_params"], res["_frames"], cfg, res["_ws"], res["_out"], d["rgb"], d["quad"],
+                            d["depth"])
+    for k in ("mean", "scale", "opacity_logit"):
+        # two sums of the same terms in another order
+        assert_grads_close(again[k].cpu().numpy(), res["grads"][k], k, rtol=GRAD_RTOL * 1e-2)
+
+
+# 16x16 and 32x8 tiles take another split of the forward and the backward from
+# 4096 tiles on: the same frames in one call and one at a time
+@pytest.mark.parametrize("tile", [(16, 16), (32, 8)])
+@pytest.mark.parametrize("n_freq", [1, 3])
+def test_large_batch_split_equals_small(tile, n_freq):
+    wl = scenes.tiny_scene(300, 167, 165, seed=9, dynamic=True, log_scale_mean=float(np.log(0.1)))
+    cfg = dataclasses.replace(wl.cfg, tile_w=tile[0], tile_h=tile[1], freqs=(30e6, 60e6, 20e6)[:n_freq])
+    F = 4096 // (cfg.tiles_x * cfg.tiles_y) + 1
+    frames = scenes.identity_frames(np.linspace(0.0, 0.2, F), 167, 165, 1.2 * 167, 1.2 * 167, cfg.n_quad,
+                                    bg_seed=3, n_freq=n_freq)
+    up = scenes.upstream_grads(F, cfg, seed=2)
+    res = run_gpu(wl.gaussians, frames, cfg, upstream=up)
+    sums = {}
+    for f in range(F):
+        one = run_gpu(wl.gaussians, frames[f:f + 1], cfg, upstream={k: v[f:f + 1] for k, v in up.items()})
+        for k in ("rgb", "quad", "depth", "T_final", "n_contrib"):
+            assert np.array_equal(one[k][0], res[k][f]), k
+        for k, v in one["grads"].items():
+            if v is not None:
+                sums[k] = sums.get(k, 0.0) + v.astype(np.float64)
+    for k, v in sums.items():
+        # float32 sums of the same terms in another order
+        assert_grads_close(res["grads"][k], v, k, rtol=GRAD_RTOL * 1e-2)
