@@ -60,7 +60,11 @@ constexpr int kMaxChunksPerBlock = 4;
 __global__ void __launch_bounds__(256) k_group_count(Params P, int C, int QC, int CPW,
                                                      const uint32_t* __restrict__ dkey,
                                                      const uint2* __restrict__ drect,
-                                                     uint32_t* __restrict__ cntA) {
+                                                     uint32_t* __restrict__ cntA, uint32_t* __restrict__ touch) {
+    // no item has been walked yet (the flags' bytes, four at a time; the
+    // workspace pads them to whole words)
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < (P.n * P.F + 3) / 4; i += (int64_t)gridDim.x * 256)
+        touch[i] = 0u;
     __shared__ uint32_t lcnt[kMaxChunksPerBlock][kMaxGroupsPerFrame];
     const Groups G = groups_of(P);
     const int TPC = 256 / CPW;   // threads per chunk
@@ -563,7 +567,7 @@ hipError_t launch_binning(const Params& P, const Workspace& w, int dbuf, hipStre
         ProfScope _p("k_group_count", s);
         const int cpw = g.C >= 512 ? 1 : (g.C >= 256 ? 2 : 4);   // 512 / C in [1, 4]
         hipLaunchKernelGGL(k_group_count, dim3((chunks + cpw - 1) / cpw), dim3(256), 0, s, P, g.C, g.QC, cpw,
-                           w.dkey[dbuf], w.drect[dbuf], w.cntA);
+                           w.dkey[dbuf], w.drect[dbuf], w.cntA, reinterpret_cast<uint32_t*>(w.touch));
     }
     if (chunks) {
         ProfScope _p("k_group_colscan", s);

@@ -245,7 +245,7 @@ int gftorf_render_bwd(const gftorf_gaussians* g, const gftorf_frame* frames, int
     hipStream_t s = static_cast<hipStream_t>(stream);
     (void)hipGetLastError();
 
-    gft::launch_fill_f32(w.grec, 0.f, (int64_t)gft::grad_floats(P.nf) * w.M, s);
+    gft::launch_clear_grec(P, w, s);
     if (d_bg) gft::launch_fill_f32(d_bg, 0.f, (int64_t)n_frames * (3 + P.nq), s);
     hipError_t e = gft::launch_composite_bwd(P, frames, w, *saved, d_rgb, d_quad,
                                              d_depth, d_bg, s);

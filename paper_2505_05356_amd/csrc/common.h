@@ -96,6 +96,7 @@ struct Workspace {
     float4* rec;            // [M][record_float4s]
     float4* conic;          // [M]
     uint32_t* cnt;          // [M] tiles covered
+    uint8_t* touch;         // [M] 1 if the forward walked the item in some tile: only those have gradients
     uint32_t* nf_block;     // [ceil(n / 256)] non-finite Gaussians per preprocess block
     uint32_t* dkey[2];      // [M] depth keys (double buffer)
     uint32_t* dval[2];      // [M] item ids
@@ -143,6 +144,7 @@ inline Workspace carve(void* base, int64_t n, int32_t F, int nf, int ntx, int nt
     w.rec = reinterpret_cast<float4*>(take(sizeof(float4) * record_float4s(nf) * M));
     w.conic = reinterpret_cast<float4*>(take(sizeof(float4) * M));
     w.cnt = reinterpret_cast<uint32_t*>(take(4 * M));
+    w.touch = reinterpret_cast<uint8_t*>(take(M));
     w.nf_block = reinterpret_cast<uint32_t*>(take(4 * (size_t)((n + 255) / 256 + 1)));
     for (int i = 0; i < 2; ++i) w.dkey[i] = reinterpret_cast<uint32_t*>(take(4 * M));
     for (int i = 0; i < 2; ++i) w.dval[i] = reinterpret_cast<uint32_t*>(take(4 * M));
@@ -217,6 +219,7 @@ hipError_t launch_composite_bwd(const Params& P, const gftorf_frame* frames, con
                                 hipStream_t s);
 void launch_preprocess_bwd(const Params& P, const gftorf_gaussians& g, const gftorf_frame* frames,
                            const Workspace& w, const gftorf_gaussians_grad& grad, hipStream_t s);
+void launch_clear_grec(const Params& P, const Workspace& w, hipStream_t s);
 void launch_fill_f32(float* p, float v, int64_t n, hipStream_t s);
 void launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);
 void launch_l2_loss(const float* pred, const float* targets, const int32_t* frame_index,

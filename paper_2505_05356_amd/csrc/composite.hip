@@ -237,6 +237,7 @@ __global__ void __launch_bounds__(64 * WPT) k_composite_fwd(Params P, const gfto
                                                             const uint32_t* __restrict__ gval,
                                                             const uint16_t* __restrict__ gloc,
                                                             uint32_t* __restrict__ tval,
+                                                            uint8_t* __restrict__ touch,
                                                             const float4* __restrict__ rec,
                                                             const float4* __restrict__ conic,
                                                             gftorf_outputs out, uint2* __restrict__ wcount) {
@@ -366,9 +367,11 @@ __global__ void __launch_bounds__(64 * WPT) k_composite_fwd(Params P, const gfto
         queued -= (uint32_t)cnt;
         // the next batch's entries are found, and their items loaded, while
         // this one is walked
+        const uint32_t walked = item;
         next_items();
         const uint32_t pos0 = pos + 1u;   // list position of the batch's first entry
-        for (int k0 = 0; k0 < cnt && any != 0ull; k0 += U) {
+        int k0 = 0;
+        for (; k0 < cnt && any != 0ull; k0 += U) {
             float a[U][PPT];
             float4 fld[U][SS4 - 2];
 #pragma unroll
@@ -424,6 +427,8 @@ __global__ void __launch_bounds__(64 * WPT) k_composite_fwd(Params P, const gfto
                     }
                 }
         }
+        // what no pixel walked has no gradient: the backward skips its record
+        if (lane < min(k0, cnt)) touch[walked] = 1;
         going = any != 0ull;
         if constexpr (SHARED) {
             const int t = (int)(pos / 64u) & 1;
@@ -709,7 +714,7 @@ hipError_t fwd_wpt(const Params& P, const gftorf_frame* frames, const Workspace&
     const unsigned blocks = (unsigned)(P.F * P.n_tiles);
 #define GFT_FWD(NF_)                                                                                          \
     hipLaunchKernelGGL((k_composite_fwd<TW, TH, NF_, WPT, U>), dim3(blocks), dim3(64 * WPT), 0, s, P, frames, \
-                       w.ranges, w.granges, w.gval, w.gloc, w.tval, w.rec, w.conic, out, w.wcount)
+                       w.ranges, w.granges, w.gval, w.gloc, w.tval, w.touch, w.rec, w.conic, out, w.wcount)
     switch (P.nf) {
         case 1: GFT_FWD(1); break;
         case 2: GFT_FWD(2); break;

@@ -70,3 +70,31 @@ def test_large_batch_split_equals_small(tile, n_freq):
     for k, v in sums.items():
         # float32 sums of the same terms in another order
         assert_grads_close(res["grads"][k], v, k, rtol=GRAD_RTOL * 1e-2)
+
+
+# the preprocess backward packs the walked Gaussians of a workgroup when it
+# has more than one round of them (here 64 Gaussians, 16 or 8 a round), and
+# writes zeros for the others: against the per-frame calls, which do not pack
+@pytest.mark.parametrize("n_frames,sh", [(9, False), (17, False), (9, True)])
+def test_packed_preprocess_backward(n_frames, sh):
+    n = 70_001
+    g = scenes.draw_gaussians(n, 64, 48, 60.0, 60.0, seed=4, dynamic=True, log_scale_mean=float(np.log(0.02)))
+    if sh:
+        g = scenes.with_sh(g, degree=2, seed=1)
+    g.delta = np.random.default_rng(0).normal(0.0, 0.01, (n_frames, 3, n)).astype(np.float32)
+    cfg = scenes.RenderConfig(width=64, height=48)
+    frames = scenes.identity_frames(np.linspace(0.0, 0.3, n_frames), 64, 48, 60.0, 60.0, 4)
+    up = scenes.upstream_grads(n_frames, cfg, seed=2)
+    res = run_gpu(g, frames, cfg, upstream=up)
+    sums = {}
+    for f in range(n_frames):
+        one = run_gpu(dataclasses.replace(g, delta=g.delta[f:f + 1].copy()), frames[f:f + 1], cfg,
+                      upstream={k: v[f:f + 1] for k, v in up.items()})
+        # float32 sums of the same terms in another order
+        assert_grads_close(res["grads"]["delta"][f], one["grads"]["delta"][0], f"delta {f}", rtol=GRAD_RTOL * 1e-2)
+        for k, v in one["grads"].items():
+            if v is not None and k != "delta":
+                sums[k] = sums.get(k, 0.0) + v.astype(np.float64)
+    assert any((v == 0).all(axis=tuple(range(v.ndim - 1))).any() for v in sums.values())   # some have no gradient
+    for k, v in sums.items():
+        assert_grads_close(res["grads"][k], v, k, rtol=GRAD_RTOL * 1e-2)
