@@ -78,32 +78,9 @@ __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// Positional encoding: feature f of the network input.  Returns the input
-// coordinate it reads (0..2 = x, 3 = t, -1 = padding) and its block: 0 = the
-// coordinate itself, 2k + 1 = sin(2^k pi p), 2k + 2 = cos(2^k pi p).
-__device__ __forceinline__ int feat_src(int f, int lx, int lt, int& blk) {
-    const int nx = 3 * (1 + 2 * lx);
-    if (f < nx) {
-        blk = f / 3;
-        return f - 3 * blk;
-    }
-    f -= nx;
-    blk = f;
-    return f < 1 + 2 * lt ? 3 : -1;
-}
-
-__device__ __forceinline__ float enc(float p, int blk) {
-    if (blk == 0) return p;
-    const float a = ldexpf(p, (blk - 1) >> 1);   // 2^k p, exact
-    return ((blk - 1) & 1) ? cospif(a) : sinpif(a);
-}
-
-__device__ __forceinline__ float enc_d(float p, int blk) {   // d enc / d p
-    if (blk == 0) return 1.0f;
-    const int k = (blk - 1) >> 1;
-    const float a = ldexpf(p, k), w = ldexpf(3.14159265358979f, k);
-    return ((blk - 1) & 1) ? -w * sinpif(a) : w * cospif(a);
-}
+// Positional encoding, the network's input features: of the scaled centre p
+// the blocks p, sin(2^k pi p), cos(2^k pi p), k = 0 .. lx - 1, of its three
+// coordinates, then the same of the scaled time.
 
 __device__ __forceinline__ float pick4(const float (&v)[4], int c) {
     return c == 0 ? v[0] : c == 1 ? v[1] : c == 2 ? v[2] : v[3];
@@ -202,14 +179,32 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int lr = lane & 15, lg = lane >> 4;
     const int64_t r0 = (int64_t)blockIdx.x * kRows;
-    {   // h_0: two threads per row, 48 features each
+    {   // h_0: two threads per row, each every other frequency (sine and cosine
+        // from one reduction); the coordinates themselves and the padding by both
         const int rr = tid >> 1, half = tid & 1;
         float xin[4];
         row_inputs(a, r0 + rr, xin);
-        for (int f = 48 * half; f < 48 * half + 48; ++f) {
-            int blk;
-            const int c = feat_src(f, a.lx, a.lt, blk);
-            X[rr * kLDX + f] = (bf16)(c < 0 ? 0.f : enc(pick4(xin, c), blk));
+        bf16* h = X + rr * kLDX;
+        const int nx = 3 * (1 + 2 * a.lx);
+        for (int k = half; k < a.lx; k += 2)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                float sn, cs;
+                sincospif(ldexpf(xin[c], k), &sn, &cs);   // 2^k p is exact
+                h[3 * (1 + 2 * k) + c] = (bf16)sn;
+                h[3 * (2 + 2 * k) + c] = (bf16)cs;
+            }
+        for (int k = half; k < a.lt; k += 2) {
+            float sn, cs;
+            sincospif(ldexpf(xin[3], k), &sn, &cs);
+            h[nx + 1 + 2 * k] = (bf16)sn;
+            h[nx + 2 + 2 * k] = (bf16)cs;
+        }
+        if (half == 0) {
+            for (int c = 0; c < 3; ++c) h[c] = (bf16)xin[c];
+            h[nx] = (bf16)xin[3];
+        } else {
+            for (int f = nx + 1 + 2 * a.lt; f < kK0; ++f) h[f] = (bf16)0.f;
         }
     }
     __syncthreads();
@@ -417,16 +412,20 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
         const int64_t r = r0 + rr;
         float xin[4];
         row_inputs(a, r, xin);
-        float s0 = 0.f, s1 = 0.f, s2 = 0.f;
-        for (int f = 48 * half; f < 48 * half + 48; ++f) {
-            int blk;
-            const int c = feat_src(f, a.lx, a.lt, blk);
-            if (c < 0 || c > 2) continue;
-            const float v = XF[rr * kLDF + f] * enc_d(pick4(xin, c), blk);
-            s0 += c == 0 ? v : 0.f;
-            s1 += c == 1 ? v : 0.f;
-            s2 += c == 2 ? v : 0.f;
+        const float* g = XF + rr * kLDF;
+        float s[3] = {0.f, 0.f, 0.f};
+        if (half == 0)
+            for (int c = 0; c < 3; ++c) s[c] = g[c];
+        for (int k = half; k < a.lx; k += 2) {
+            const float w = ldexpf(3.14159265358979f, k);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                float sn, cs;
+                sincospif(ldexpf(xin[c], k), &sn, &cs);
+                s[c] += g[3 * (1 + 2 * k) + c] * (w * cs) - g[3 * (2 + 2 * k) + c] * (w * sn);
+            }
         }
+        float s0 = s[0], s1 = s[1], s2 = s[2];
         s0 += __shfl_xor(s0, 1, 64);
         s1 += __shfl_xor(s1, 1, 64);
         s2 += __shfl_xor(s2, 1, 64);
