@@ -9,8 +9,9 @@
 //                 zero-padded so every product is whole 16 x 16 x 32 tiles.
 //   k_mlp_fwd     one workgroup of 4 waves per 128 rows: the encoding and
 //                 every layer's activations stay in LDS (128 x 256 bf16),
-//                 weights stream from L2; wave w computes output columns
-//                 64w .. 64w+63 of all 128 rows with v_mfma_f32_16x16x32_bf16.
+//                 weights stream from L2, two k-steps ahead; wave w computes
+//                 output features 64w .. 64w+63 of all 128 rows with
+//                 v_mfma_f32_16x16x32_bf16, the weights as the A operand.
 //                 Two workgroups share a CU (two waves per SIMD), so one's
 //                 epilogue overlaps the other's products.  Training mode also
 //                 stores h_0 .. h_8 and the ReLU decisions as bits.
@@ -20,18 +21,28 @@
 //                 scaled centre input.  Two workgroups per CU, as the forward.
 //   k_mlp_dw      dW_l = sum_rows gz_l h_l^T, db_l = sum_rows gz_l: rows are the
 //                 contraction, split into fixed chunks, one partial per chunk;
-//                 each 64-row stage of gz_l and h_l passes once through LDS.
+//                 each 64-row stage of gz_l and h_l passes once through LDS,
+//                 which transposes the fragments as they are read.
 //   k_mlp_reduce  sums the chunk partials in chunk order into the parameter
 //                 layout; k_mlp_dx0 sums the centre gradient over the times.
 //   k_blend       Eq. 7 with the network: per-frame offsets from the offsets
 //                 at two integer timesteps; k_blend_bwd is its transpose.
 //
-// Saved activations and gradients use a row-blocked layout [rows/8][feat][8]:
-// the eight rows of one feature are one 16-byte fragment of the weight-gradient
-// product, and the row-parallel kernels write four of them per lane.  The
-// forward also keeps the ReLU decisions of h_1 .. h_8 as bits, 16 bytes per
-// lane and layer in the lane's own accumulator order, so the backward gates
-// its gradients from 4 registers instead of re-reading the activations.
+// With the weights as the A operand a lane holds four consecutive features of
+// a row, so the epilogues write LDS by 8 bytes (32 writes per layer and lane
+// instead of 128 of 2 bytes) and the ReLU and its bits cost 8 instructions per
+// four elements (16 before).  Activations and gradients are saved row-major,
+// as LDS holds them, by whole cache lines and past L2 (non-temporal), where
+// the weights stay.  Loads and stores retire in order, so the two k-steps of
+// weights that the next layer starts with are loaded before the stores.
+// 1.6M rows: forward 2.09 -> 1.92 ms (without saves 1.47 -> 1.37 ms, 1.13
+// PFLOP/s, where a large library product reaches 1.20 on the same card),
+// backward 2.49 -> 2.36 ms.  What is left of both is the stores: 1.3 ms
+// alone, at the rate of a plain fill, and 1.7 ms the products alone.
+//
+// The forward also keeps the ReLU decisions of h_1 .. h_8 as bits, 16 bytes
+// per lane and layer in the lane's own accumulator order, so the backward
+// gates its gradients from 4 registers instead of re-reading the activations.
 #include <mutex>
 
 #include "mlp.h"
@@ -52,6 +63,9 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x2 __attribute__((ext_vector_type(2)));
+
+// Third word of a raw buffer descriptor (32-bit untyped elements).
+constexpr int kBufferWord3 = 0x00020000;
 
 // LDS row stride in bf16: the 16-byte pad puts the 16 rows of one fragment
 // read in 16 distinct 4-bank groups.
@@ -96,54 +110,100 @@ __device__ __forceinline__ void row_inputs(const Args& a, int64_t r, float (&xin
     xin[3] = a.st * (a.frames ? a.frames[t].time : a.times[t]);
 }
 
-// acc[r][c] += X[16 r + .][.] * B[col0 + 16 c + .][.] over K: X in LDS
-// (row-major, stride kLDX), B in global memory as [cols][K].
-// With PIPE the next k-step's weight fragments are in flight while this one
-// multiplies (pinned by a scheduling barrier); without it the compiler
-// schedules the loads, which suits the backward, whose mask loads are
-// already queued ahead of the product.
-template <int K, bool PIPE>
-__device__ __forceinline__ void gemm_128x64(const bf16* X, const bf16* __restrict__ B, int col0,
-                                            f32x4 (&acc)[8][4], int lane) {
-    const int lr = lane & 15, lk = (lane >> 4) * 8;
-    const bf16* bp = B + (size_t)(col0 + lr) * K + lk;
-    bf16x8 b[4], bn[4];
+// acc[r][c] += W[col0 + 16 c + .][.] * X[16 r + .][.]^T over K: X in LDS
+// (row-major, stride kLDX), W in global memory as [features][K].  The weights
+// are the A operand, so a lane receives four consecutive features of one row
+// (row 16 r + l % 16, features col0 + 16 c + 4 (l / 16) + j), which it writes
+// back to LDS and gates with 8-byte accesses.
+// The next k-step's weight fragments are in flight while this one multiplies
+// (pinned by a scheduling barrier).
+// `w` holds the first D k-steps' weight fragments (first_weights), which the
+// caller loads before the previous layer's stores.
+template <int K, int D>
+__device__ __forceinline__ void first_weights(const bf16* __restrict__ W, int col0, bf16x8 (&w)[D][4], int lane) {
+    const bf16* wp = W + (size_t)(col0 + (lane & 15)) * K + (lane >> 4) * 8;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) b[c] = *(const bf16x8*)(bp + (size_t)16 * c * K);
+    for (int d = 0; d < D && 32 * d < K; ++d)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) w[d][c] = *(const bf16x8*)(wp + (size_t)16 * c * K + 32 * d);
+}
+
+template <int K, int D>
+__device__ __forceinline__ void gemm_128x64(const bf16* X, const bf16* __restrict__ W, int col0,
+                                            f32x4 (&acc)[8][4], bf16x8 (&w)[D][4], int lane) {
+    const int lr = lane & 15, lk = (lane >> 4) * 8;
+    const bf16* wp = W + (size_t)(col0 + lr) * K + lk;
+    bf16x8 wn[4];
 #pragma unroll
     for (int k0 = 0; k0 < K; k0 += 32) {
-        if (k0 + 32 < K) {
+        if (k0 + 32 * D < K) {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) bn[c] = *(const bf16x8*)(bp + (size_t)16 * c * K + k0 + 32);
+            for (int c = 0; c < 4; ++c) wn[c] = *(const bf16x8*)(wp + (size_t)16 * c * K + k0 + 32 * D);
         }
-        if (PIPE) __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
             const bf16x8 x = *(const bf16x8*)(X + (16 * r + lr) * kLDX + lk + k0);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc[r][c] = mfma(x, b[c], acc[r][c]);
+            for (int c = 0; c < 4; ++c) acc[r][c] = mfma(w[0][c], x, acc[r][c]);
         }
-        if (k0 + 32 < K) {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) b[c] = bn[c];
+        for (int c = 0; c < 4; ++c) {
+#pragma unroll
+            for (int d = 0; d + 1 < D; ++d) w[d][c] = w[d + 1][c];
+            if (k0 + 32 * D < K) w[D - 1][c] = wn[c];
         }
     }
 }
 
-// Bit of element j of accumulator row tile r in its column tile's mask word.
-// The forward derives the four bits of a tile from the two 32-bit words of its
-// bfloat16 ReLU outputs (each half non-negative): adding 0x7fff to a half sets
-// its bit 15 exactly when the half is non-zero, without carrying into the
-// other half; bits 15 and 31 of the two sums then shift into place together.
-__device__ __forceinline__ constexpr int mask_bit(int r, int j) {
-    return r + (j == 0 ? 0 : j == 1 ? 16 : j == 2 ? 8 : 24);
+// Writes the first K columns of the LDS rows to `dst`, row-major [128][K],
+// between a product that reads them and the barrier after it: the stores
+// complete under the epilogue, and no weight load waits behind them (loads and
+// stores retire in order).  K / 8 lanes write a row's 16-byte pieces, so whole
+// cache lines leave together.
+template <int K>
+__device__ __forceinline__ void save_rows(const bf16* X, bf16* __restrict__ dst, int tid) {
+    constexpr int P = K / 8, N = 128 * P / 256;   // pieces per row, and per thread
+    // four in flight, none of them hoisted into the product (whose registers
+    // leave no room), and one lane offset for all of them (buffer addressing)
+    __builtin_amdgcn_sched_barrier(0);
+    const __amdgpu_buffer_rsrc_t out =
+        __builtin_amdgcn_make_buffer_rsrc(dst, 0, 128 * K * (int)sizeof(bf16), kBufferWord3);
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int q0 = 0; q0 < N; q0 += 4) {
+        u32x4 v[4];
+#pragma unroll
+        for (int q = q0; q < q0 + 4 && q < N; ++q) {
+            const int i = tid + 256 * q;
+            v[q - q0] = *(const u32x4*)(X + i / P * kLDX + i % P * 8);
+        }
+#pragma unroll
+        for (int q = q0; q < q0 + 4 && q < N; ++q)
+            __builtin_amdgcn_raw_buffer_store_b128(v[q - q0], out, 16 * tid, 16 * 256 * q, 2);
+        __builtin_amdgcn_sched_barrier(0);
+    }
 }
 
-__device__ __forceinline__ uint32_t relu_bits(bf16x4 v, int r) {
-    const uint2 d = __builtin_bit_cast(uint2, v);
-    const uint32_t s0 = (d.x + 0x7fff7fffu) & 0x80008000u;   // j = 0 at bit 15, j = 1 at bit 31
-    const uint32_t s1 = (d.y + 0x7fff7fffu) & 0x80008000u;   // j = 2, j = 3
-    return (s0 >> (15 - r)) | (s1 >> (7 - r));
+// Two float32 to a packed pair of bfloat16, round to nearest even.
+__device__ __forceinline__ uint32_t pack2(float a, float b) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+
+// Bit of element j of accumulator row tile r in its column tile's mask word.
+// The forward takes the four bits of a tile from the two 32-bit words of its
+// bfloat16 ReLU outputs (each half a non-negative int16, non-zero if active):
+// the smaller of each half and 1, the second word's beside the first's.
+__device__ __forceinline__ constexpr int mask_bit(int r, int j) { return 2 * r + (j >> 1) + 16 * (j & 1); }
+
+__device__ __forceinline__ uint32_t relu_bits(uint2 v, int r) {
+    // (as an instruction: the compiler would make two compares and selects of it)
+    uint32_t lo, hi;
+    asm("v_pk_min_i16 %0, %1, %2" : "=v"(lo) : "v"(v.x), "s"(0x00010001));
+    asm("v_pk_min_i16 %0, %1, %2" : "=v"(hi) : "v"(v.y), "s"(0x00010001));
+    return (lo | (hi << 1)) << (2 * r);
 }
 
 __device__ __forceinline__ void zero(f32x4 (&acc)[8][4]) {
@@ -153,30 +213,10 @@ __device__ __forceinline__ void zero(f32x4 (&acc)[8][4]) {
         for (int c = 0; c < 4; ++c) acc[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
-// offset (in bf16) of rows row .. row+3 (row % 4 == 0) of feature col in a
-// row-blocked [rows/8][F][8] array
-template <int F>
-__device__ __forceinline__ size_t blk_off(int64_t row, int col) {
-    return ((size_t)(row >> 3) * F + col) * 8 + (size_t)(row & 7);
-}
-
-// copy the first F columns of the 128 LDS rows to a row-blocked array
-template <int F>
-__device__ __forceinline__ void save_block(const bf16* X, bf16* __restrict__ dst, int64_t r0,
-                                           int tid) {
-    for (int p = tid; p < 16 * F; p += 256) {
-        const int rb = p / F, f = p - rb * F;
-        bf16x8 v;
-#pragma unroll
-        for (int m = 0; m < 8; ++m) v[m] = X[(8 * rb + m) * kLDX + f];
-        *(bf16x8*)(dst + ((size_t)(r0 / 8 + rb) * F + f) * 8) = v;
-    }
-}
-
 template <bool SAVE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_mlp_fwd(Args a, float* __restrict__ delta) {
     __shared__ __attribute__((aligned(16))) bf16 X[kRows * kLDX];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane & 15, lg = lane >> 4;
     const int64_t r0 = (int64_t)blockIdx.x * kRows;
     {   // h_0: two threads per row, each every other frequency (sine and cosine
@@ -208,49 +248,52 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
         }
     }
     __syncthreads();
-    if (SAVE) save_block<kK0>(X, a.H[0], r0, tid);
-
     f32x4 acc[8][4];
     const int col0 = 64 * wv;
-    for (int l = 0; l < kDepth; ++l) {
-        // the products accumulate onto the bias
+    bf16x8 w[2][4];
+    first_weights<kK0>(a.wf[0], col0, w, lane);
+    auto bias = [&](int l) {   // the products accumulate onto the bias
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const float bb = a.bias[l][col0 + 16 * c + lr];
+            const float* bb = a.bias[l] + col0 + 16 * c + 4 * lg;
+            const f32x4 bv = {bb[0], bb[1], bb[2], bb[3]};
 #pragma unroll
-            for (int r = 0; r < 8; ++r) acc[r][c] = f32x4{bb, bb, bb, bb};
+            for (int r = 0; r < 8; ++r) acc[r][c] = bv;
         }
-        if (l == 0)
-            gemm_128x64<kK0, true>(X, a.wf[0], col0, acc, lane);
-        else
-            gemm_128x64<kWidth, true>(X, a.wf[l], col0, acc, lane);
+    };
+    auto activate = [&](int l) {   // h_{l+1} = relu(acc), into LDS
         __syncthreads();   // every wave has read this layer's input
-        // rows r0 + 16 r + 4 lg .. +3 of feature col0 + 16 c + lr sit at
-        // hb + (16 r / 8) * kWidth * 8 + 16 c * 8 in the row-blocked layout
-        bf16* hb = a.H[l + 1] + ((size_t)(r0 / 8 + (lg >> 1)) * kWidth + col0 + lr) * 8 + 4 * (lg & 1);
         uint32_t mw[4] = {0u, 0u, 0u, 0u};
+        bf16* xo = X + lr * kLDX + col0 + 4 * lg;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const int col = col0 + 16 * c + lr;
 #pragma unroll
             for (int r = 0; r < 8; ++r) {
                 // bfloat16 first, then ReLU as a packed 16-bit integer max with 0:
                 // a negative bfloat16 is a negative int16
-                const bf16x4 z = __builtin_convertvector(acc[r][c], bf16x4);
-                const s16x4 zi = __builtin_bit_cast(s16x4, z);
-                const bf16x4 v = __builtin_bit_cast(bf16x4, __builtin_elementwise_max(zi, s16x4{0, 0, 0, 0}));
-#pragma unroll
-                for (int j = 0; j < 4; ++j) X[(16 * r + 4 * lg + j) * kLDX + col] = v[j];
-                if (SAVE) {
-                    *(bf16x4*)(hb + (size_t)r * (2 * kWidth * 8) + c * 128) = v;
-                    mw[c] |= relu_bits(v, r);
-                }
+                uint2 v = make_uint2(pack2(acc[r][c][0], acc[r][c][1]), pack2(acc[r][c][2], acc[r][c][3]));
+                asm("v_pk_max_i16 %0, %1, 0" : "=v"(v.x) : "v"(v.x));
+                asm("v_pk_max_i16 %0, %1, 0" : "=v"(v.y) : "v"(v.y));
+                *(uint2*)(xo + 16 * r * kLDX + 16 * c) = v;
+                if (SAVE) mw[c] |= relu_bits(v, r);
             }
         }
         if (SAVE) a.mask[((size_t)blockIdx.x * kDepth + l) * 256 + tid] = make_uint4(mw[0], mw[1], mw[2], mw[3]);
         __syncthreads();
+    };
+    bias(0);
+    gemm_128x64<kK0>(X, a.wf[0], col0, acc, w, lane);
+    first_weights<kWidth>(a.wf[1], col0, w, lane);
+    if (SAVE) save_rows<kK0>(X, a.H[0] + (size_t)r0 * kK0, tid);
+    activate(0);
+    for (int l = 1; l < kDepth; ++l) {
+        bias(l);
+        gemm_128x64<kWidth>(X, a.wf[l], col0, acc, w, lane);
+        if (l + 1 < kDepth) first_weights<kWidth>(a.wf[l + 1], col0, w, lane);
+        if (SAVE) save_rows<kWidth>(X, a.H[l] + (size_t)r0 * kWidth, tid);
+        activate(l);
     }
-    // head: 128 rows x 16 (3 real) outputs; wave w takes rows 32w .. 32w+31
+    // head: 16 (3 real) outputs x 128 rows; wave w takes rows 32w .. 32w+31
     f32x4 o2[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
     const bf16* bp = a.wf[kDepth] + (size_t)lr * kWidth + 8 * lg;
 #pragma unroll 4
@@ -259,29 +302,28 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
             const bf16x8 x = *(const bf16x8*)(X + (32 * wv + 16 * r + lr) * kLDX + 8 * lg + k0);
-            o2[r] = mfma(x, b, o2[r]);
+            o2[r] = mfma(b, x, o2[r]);
         }
     }
-    if (lr < 3) {
-        const float bb = a.bias[kDepth][lr];
+    if (SAVE) save_rows<kWidth>(X, a.H[kDepth] + (size_t)r0 * kWidth, tid);
+    if (lg == 0) {   // the lane's first four outputs of its row: three are real
 #pragma unroll
-        for (int r = 0; r < 2; ++r)
+        for (int r = 0; r < 2; ++r) {
+            const int64_t row = r0 + 32 * wv + 16 * r + lr;
+            if (row < a.rows) {
+                const int t = (int)(row / a.n);
+                const int64_t k = row - (int64_t)t * a.n;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int64_t row = r0 + 32 * wv + 16 * r + 4 * lg + j;
-                if (row < a.rows) {
-                    const int t = (int)(row / a.n);
-                    const int64_t k = row - (int64_t)t * a.n;
-                    delta[((int64_t)t * 3 + lr) * a.n + k] = o2[r][j] + bb;
-                }
+                for (int j = 0; j < 3; ++j) delta[((int64_t)t * 3 + j) * a.n + k] = o2[r][j] + a.bias[kDepth][j];
             }
+        }
     }
 }
 
 // The ReLU decisions of the training forward as plain bytes, dec[row][layer][unit]
 // (1 = active), read from (WRITE = false) or written into (WRITE = true) the
 // bit words: one thread per word, i.e. per (128-row block, layer, forward
-// thread), which holds the thread's 4 column tiles x 8 row tiles x 4 rows.
+// thread), which holds the thread's 4 column tiles x 8 row tiles x 4 features.
 // Padding rows read nothing and are written inactive.
 template <bool WRITE>
 __global__ void __launch_bounds__(256) k_mlp_decisions(uint4* __restrict__ mask, uint8_t* __restrict__ dec,
@@ -298,12 +340,11 @@ __global__ void __launch_bounds__(256) k_mlp_decisions(uint4* __restrict__ mask,
         mw[0] = m.x, mw[1] = m.y, mw[2] = m.z, mw[3] = m.w;
     }
     for (int c = 0; c < 4; ++c) {
-        const int col = 64 * wv + 16 * c + lr;
         for (int r = 0; r < 8; ++r)
             for (int j = 0; j < 4; ++j) {
-                const int64_t row = blk * kRows + 16 * r + 4 * lg + j;
+                const int64_t row = blk * kRows + 16 * r + lr;
                 if (row >= rows) continue;
-                uint8_t* d = dec + (row * kDepth + l) * kWidth + col;
+                uint8_t* d = dec + (row * kDepth + l) * kWidth + 64 * wv + 16 * c + 4 * lg + j;
                 if (WRITE)
                     mw[c] |= (*d != 0 ? 1u : 0u) << mask_bit(r, j);
                 else
@@ -316,7 +357,7 @@ __global__ void __launch_bounds__(256) k_mlp_decisions(uint4* __restrict__ mask,
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_mlp_bwd(Args a, const float* __restrict__ d_delta,
                                                  float* __restrict__ dxr) {
     __shared__ __attribute__((aligned(16))) bf16 X[kRows * kLDX];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane & 15, lg = lane >> 4;
     const int64_t r0 = (int64_t)blockIdx.x * kRows;
     {   // gz_8 = dL/d delta of the block's rows, padded to kHeadK columns
@@ -332,7 +373,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
             X[rr * kLDX + c] = (bf16)(c < 3 ? pick4(g, c) : 0.f);
     }
     __syncthreads();
-    save_block<kOutPad>(X, a.GZ[kDepth], r0, tid);
+    // two threads per row: its 16 padded columns
+    *(bf16x8*)(a.GZ[kDepth] + (size_t)(r0 + (tid >> 1)) * kOutPad + 8 * (tid & 1)) =
+        *(const bf16x8*)(X + (tid >> 1) * kLDX + 8 * (tid & 1));
 
     f32x4 acc[8][4];
     const int col0 = 64 * wv;
@@ -340,40 +383,37 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     // before the product so that their latency hides behind it
     uint4 hm;
     auto load_masks = [&](int l) { hm = a.mask[((size_t)blockIdx.x * kDepth + l) * 256 + tid]; };
-    // rows r0 + 16 r + 4 lg .. +3 of feature col0 + 16 c + lr of a row-blocked
-    // array sit at base + r * 2 kWidth 8 + c * 128
-    const size_t base = ((size_t)(r0 / 8 + (lg >> 1)) * kWidth + col0 + lr) * 8 + 4 * (lg & 1);
     load_masks(kDepth - 1);
     zero(acc);
-    gemm_128x64<kHeadK, false>(X, a.wt[kDepth], col0, acc, lane);   // g_8 = gz_8 W_8
+    bf16x8 w[2][4];
+    first_weights<kHeadK>(a.wt[kDepth], col0, w, lane);
+    gemm_128x64<kHeadK>(X, a.wt[kDepth], col0, acc, w, lane);   // g_8 = gz_8 W_8
+    first_weights<kWidth>(a.wt[kDepth - 1], col0, w, lane);
     for (int l = kDepth - 1; l >= 0; --l) {
         __syncthreads();
         // gz_l = g_{l+1} * [h_{l+1} > 0]
-        bf16* gzb = a.GZ[l] + base;
         const uint32_t mw[4] = {hm.x, hm.y, hm.z, hm.w};
+        bf16* xo = X + lr * kLDX + col0 + 4 * lg;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const int col = col0 + 16 * c + lr;
 #pragma unroll
             for (int r = 0; r < 8; ++r) {
-                const size_t o = (size_t)r * (2 * kWidth * 8) + c * 128;
                 // bfloat16 first, then the gates as 16-bit masks: shifting the
                 // word puts the bits of elements (0, 1), then (2, 3), at bits 15
                 // and 31, and an arithmetic shift of each half by 15 spreads them
-                uint2 z = __builtin_bit_cast(uint2, __builtin_convertvector(acc[r][c], bf16x4));
-                z.x &= __builtin_bit_cast(uint32_t, __builtin_bit_cast(s16x2, mw[c] << (15 - r)) >> (short)15);
-                z.y &= __builtin_bit_cast(uint32_t, __builtin_bit_cast(s16x2, mw[c] << (7 - r)) >> (short)15);
-                const bf16x4 v = __builtin_bit_cast(bf16x4, z);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) X[(16 * r + 4 * lg + j) * kLDX + col] = v[j];
-                *(bf16x4*)(gzb + o) = v;
+                uint2 z = make_uint2(pack2(acc[r][c][0], acc[r][c][1]), pack2(acc[r][c][2], acc[r][c][3]));
+                z.x &= __builtin_bit_cast(uint32_t, __builtin_bit_cast(s16x2, mw[c] << (15 - 2 * r)) >> (short)15);
+                z.y &= __builtin_bit_cast(uint32_t, __builtin_bit_cast(s16x2, mw[c] << (14 - 2 * r)) >> (short)15);
+                *(uint2*)(xo + 16 * r * kLDX + 16 * c) = z;
             }
         }
         __syncthreads();
         if (l > 0) {
             load_masks(l - 1);
             zero(acc);
-            gemm_128x64<kWidth, false>(X, a.wt[l], col0, acc, lane);   // g_l = gz_l W_l
+            gemm_128x64<kWidth>(X, a.wt[l], col0, acc, w, lane);   // g_l = gz_l W_l
+            if (l > 1) first_weights<kWidth>(a.wt[l - 1], col0, w, lane);
+            save_rows<kWidth>(X, a.GZ[l] + (size_t)r0 * kWidth, tid);
         }
     }
     // g_0 = gz_0 W_0 -> [128][96]: wave w takes rows 32w .. 32w+31, all 6 column tiles
@@ -393,10 +433,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
             for (int r = 0; r < 2; ++r) {
                 const bf16x8 x = *(const bf16x8*)(X + (32 * wv + 16 * r + lr) * kLDX + 8 * lg + k0);
 #pragma unroll
-                for (int c = 0; c < 6; ++c) g0[r][c] = mfma(x, b[c], g0[r][c]);
+                for (int c = 0; c < 6; ++c) g0[r][c] = mfma(b[c], x, g0[r][c]);
             }
         }
     }
+    save_rows<kWidth>(X, a.GZ[0] + (size_t)r0 * kWidth, tid);
     __syncthreads();
     constexpr int kLDF = kK0 + 4;   // float stride of g_0 in LDS
     float* XF = reinterpret_cast<float*>(X);
@@ -404,8 +445,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     for (int r = 0; r < 2; ++r)
 #pragma unroll
         for (int c = 0; c < 6; ++c)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) XF[(32 * wv + 16 * r + 4 * lg + j) * kLDF + 16 * c + lr] = g0[r][c][j];
+            *(f32x4*)(XF + (32 * wv + 16 * r + lr) * kLDF + 16 * c + 4 * lg) = g0[r][c];
     __syncthreads();
     {   // d(scaled centre) = sum over the x features of g_0 * d enc / d p; two threads per row
         const int rr = tid >> 1, half = tid & 1;
@@ -447,23 +487,33 @@ struct DwArgs {
     float* part;
 };
 
-template <int NO, int NI, int OG, int IG>
-__global__ void __launch_bounds__(512) k_mlp_dw(DwArgs d, int l0) {
+// bf16 of one staged row, padded to a stride that puts eight consecutive
+// rows' 32 bytes in distinct banks
+__host__ __device__ constexpr int staged_row(int features) { return features + (features % 32 == 16 ? 0 : 16); }
+constexpr int dw_lds(int no, int ni) { return 2 * 64 * (staged_row(no) + staged_row(ni)); }   // two stages
+
+// NO x NI of the FO x FI weights of layer l, from output oo and input ii.
+template <int NO, int NI, int OG, int IG, int FO, int FI>
+__device__ __forceinline__ void dw_chunk(const DwArgs& d, int l, int oo, int ii, bf16* lds) {
     constexpr int MT = NO / 16 / OG, NT = NI / 16 / IG;
     static_assert(OG * IG == 8 && MT * 16 * OG == NO && NT * 16 * IG == NI, "tiling");
-    // One stage is two k-steps of 32 rows = 8 row blocks of gz (NO features)
-    // and h (NI features), 16 bytes per (row block, feature): staged once per
-    // workgroup in LDS, double-buffered, and read from there by the 8 waves
-    // (each gradient tile is read by IG waves and each activation tile by OG).
-    constexpr int NC = 8 * (NO + NI);
+    // One stage is two k-steps of 32 rows of gz (NO features) and h (NI
+    // features), row-major as saved: staged once per workgroup in LDS,
+    // double-buffered, and read from there by the 8 waves (each gradient tile
+    // is read by IG waves and each activation tile by OG).  The contraction
+    // runs over the rows, so the fragments are transposed as they are read
+    // (ds_read_b64_tr_b16: four rows of 16 features, a lane per feature).
+    constexpr int SO = staged_row(NO), SI = staged_row(NI);
+    static_assert(SO / 2 % 16 == 8 && SI / 2 % 16 == 8, "row strides of an odd number of 8-bank steps");
+    constexpr int CO = NO / 8, CI = NI / 8;           // 16-byte chunks per row
+    constexpr int NC = 64 * (CO + CI);
     constexpr int PER = (NC + 511) / 512;
-    __shared__ bf16x8 sbuf[2][NC];
-    const int l = l0 + blockIdx.y;
+    auto sbuf = [&](int b) { return lds + b * (64 * (SO + SI)); };
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int lr = lane & 15, lg = lane >> 4;
     const int o0 = (wv / IG) * MT * 16, i0 = (wv % IG) * NT * 16;
-    const bf16* __restrict__ GZ = d.GZ[l];
-    const bf16* __restrict__ H = d.H[l];
+    const bf16* __restrict__ GZ = d.GZ[l] + oo;
+    const bf16* __restrict__ H = d.H[l] + ii;
     const int64_t rs = (int64_t)blockIdx.x * d.rows_per_chunk;
     const int64_t re = min(rs + d.rows_per_chunk, d.rows_pad);   // both multiples of 64
     const int nk = rs < re ? (int)((re - rs) / 64) : 0;          // stages; chunks hold multiples of 64 rows
@@ -480,19 +530,21 @@ __global__ void __launch_bounds__(512) k_mlp_dw(DwArgs d, int l0) {
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    // chunk q < 8 NO: gz row block q / NO, feature q % NO; else h likewise
+    // chunk q < 64 CO: gz row q / CO, features 8 (q % CO) ..; else h likewise
     bf16x8 stg[PER];
-    auto fetch = [&](int64_t kb) {
+    auto fetch = [&](int64_t row) {
 #pragma unroll
         for (int p = 0; p < PER; ++p) {
             const int q = tid + 512 * p;
             if (q < NC) {
-                if (q < 8 * NO) {
-                    const int rb = q / NO, f = q - rb * NO;
-                    stg[p] = *(const bf16x8*)(GZ + ((size_t)(kb + rb) * NO + f) * 8);
+                if (q < 64 * CO) {
+                    // whole rows are one run of chunks
+                    const size_t at = NO == FO ? (size_t)q * 8 : (size_t)(q / CO) * FO + q % CO * 8;
+                    stg[p] = *(const bf16x8*)(GZ + (size_t)row * FO + at);
                 } else {
-                    const int qh = q - 8 * NO, rb = qh / NI, f = qh - rb * NI;
-                    stg[p] = *(const bf16x8*)(H + ((size_t)(kb + rb) * NI + f) * 8);
+                    const int qh = q - 64 * CO;
+                    const size_t at = NI == FI ? (size_t)qh * 8 : (size_t)(qh / CI) * FI + qh % CI * 8;
+                    stg[p] = *(const bf16x8*)(H + (size_t)row * FI + at);
                 }
             }
         }
@@ -501,31 +553,43 @@ __global__ void __launch_bounds__(512) k_mlp_dw(DwArgs d, int l0) {
 #pragma unroll
         for (int p = 0; p < PER; ++p) {
             const int q = tid + 512 * p;
-            if (q < NC) sbuf[b][q] = stg[p];
+            if (q < NC) {
+                const int qh = q - 64 * CO;
+                const int at = q < 64 * CO ? q / CO * SO + q % CO * 8 : 64 * SO + qh / CI * SI + qh % CI * 8;
+                *(bf16x8*)(sbuf(b) + at) = stg[p];
+            }
         }
     };
-    const int64_t kb0 = rs / 8;
+    // this lane's fragment of 16 features from f0 over 32 rows: rows 4 lg .. +3
+    // and 16 + 4 lg .. +3, the same order for both operands
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    auto fragment = [&](const bf16* s0, int stride, int f0) {
+        const bf16* at = s0 + (4 * lg + (lr >> 2)) * stride + f0 + 4 * (lr & 3);
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)at);
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(at + 16 * stride));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
     if (nk > 0) {
-        fetch(kb0);
+        fetch(rs);
         stage(0);
     }
     __syncthreads();
     for (int k = 0; k < nk; ++k) {
         const int cur = k & 1;
         const bool more = k + 1 < nk;
-        if (more) fetch(kb0 + 8 * (k + 1));   // in flight during this stage's products
+        if (more) fetch(rs + 64 * (k + 1));   // in flight during this stage's products
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             bf16x8 av[MT], bv[NT];
 #pragma unroll
-            for (int m = 0; m < MT; ++m) av[m] = sbuf[cur][(4 * h + lg) * NO + o0 + 16 * m + lr];
+            for (int m = 0; m < MT; ++m) av[m] = fragment(sbuf(cur) + 32 * h * SO, SO, o0 + 16 * m);
 #pragma unroll
-            for (int t = 0; t < NT; ++t) bv[t] = sbuf[cur][8 * NO + (4 * h + lg) * NI + i0 + 16 * t + lr];
+            for (int t = 0; t < NT; ++t) bv[t] = fragment(sbuf(cur) + 64 * SO + 32 * h * SI, SI, i0 + 16 * t);
 #pragma unroll
             for (int m = 0; m < MT; ++m)
 #pragma unroll
                 for (int t = 0; t < NT; ++t) acc[m][t] = mfma(av[m], bv[t], acc[m][t]);
-            if (i0 == 0)
+            if (ii + i0 == 0)
 #pragma unroll
                 for (int m = 0; m < MT; ++m) ab[m] = mfma(av[m], ones, ab[m]);
         }
@@ -539,13 +603,30 @@ __global__ void __launch_bounds__(512) k_mlp_dw(DwArgs d, int l0) {
         for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                P[(size_t)(o0 + 16 * m + 4 * lg + j) * NI + i0 + 16 * t + lr] = acc[m][t][j];
-    if (i0 == 0 && lr == 0) {
+                P[(size_t)(oo + o0 + 16 * m + 4 * lg + j) * FI + ii + i0 + 16 * t + lr] = acc[m][t][j];
+    if (ii + i0 == 0 && lr == 0) {
 #pragma unroll
         for (int m = 0; m < MT; ++m)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) P[(size_t)NO * NI + o0 + 16 * m + 4 * lg + j] = ab[m][j];
+            for (int j = 0; j < 4; ++j) P[(size_t)FO * FI + oo + o0 + 16 * m + 4 * lg + j] = ab[m][j];
     }
+}
+
+// The seven square layers (grid y).
+__global__ void __launch_bounds__(512) k_mlp_dw(DwArgs d) {
+    __shared__ __attribute__((aligned(16))) bf16 lds[dw_lds(kWidth, kWidth)];
+    dw_chunk<kWidth, kWidth, 4, 2, kWidth, kWidth>(d, 1 + blockIdx.y, 0, 0, lds);
+}
+
+// The input layer and the head, each in two halves (grid y): 576 workgroups
+// of which two share a CU.  With one workgroup per chunk and layer, in two
+// launches, 112 of the 256 CUs were idle: 507 us for 1.6M rows.
+__global__ void __launch_bounds__(512) k_mlp_dw_ends(DwArgs d) {
+    __shared__ __attribute__((aligned(16))) bf16 lds[dw_lds(kWidth / 2, kK0)];
+    static_assert(dw_lds(kOutPad, kWidth / 2) <= dw_lds(kWidth / 2, kK0), "the head's stages fit");
+    const int half = (blockIdx.y & 1) * (kWidth / 2);
+    if (blockIdx.y < 2) dw_chunk<kWidth / 2, kK0, 4, 2, kWidth, kK0>(d, 0, half, 0, lds);
+    else dw_chunk<kOutPad, kWidth / 2, 1, 8, kOutPad, kWidth>(d, kDepth, 0, half, lds);
 }
 
 struct RedArgs {
@@ -845,9 +926,8 @@ hipError_t launch_bwd(const Layout& L, const Call& c, const float* d_delta, floa
     {
         ProfScope _w("k_mlp_dw", s);
         const unsigned nc = (unsigned)L.n_chunks;
-        hipLaunchKernelGGL((k_mlp_dw<kWidth, kWidth, 4, 2>), dim3(nc, kDepth - 1), dim3(512), 0, s, d, 1);
-        hipLaunchKernelGGL((k_mlp_dw<kWidth, kK0, 4, 2>), dim3(nc, 1), dim3(512), 0, s, d, 0);
-        hipLaunchKernelGGL((k_mlp_dw<kOutPad, kWidth, 1, 8>), dim3(nc, 1), dim3(512), 0, s, d, kDepth);
+        hipLaunchKernelGGL(k_mlp_dw, dim3(nc, kDepth - 1), dim3(512), 0, s, d);
+        hipLaunchKernelGGL(k_mlp_dw_ends, dim3(nc, 4), dim3(512), 0, s, d);
     }
     RedArgs r;
     for (int l = 0; l < kLayers; ++l) {
