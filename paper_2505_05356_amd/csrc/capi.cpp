@@ -198,7 +198,7 @@ int gftorf_profile_end(gftorf_profile_entry* out, int32_t max_entries, int32_t* 
 size_t gftorf_workspace_size(int64_t n, int32_t n_frames, const gftorf_config* cfg) {
     gft::Params P;
     if (build_params(n, n_frames, cfg, &P) != GFTORF_OK) return 0;
-    return gft::carve(nullptr, n, n_frames, P.nf, P.ntx, P.nty, P.cap).bytes;
+    return gft::carve(nullptr, n, n_frames, P.nf, P.ntx, P.nty, P.tw * P.th, P.cap).bytes;
 }
 
 int gftorf_render_fwd(const gftorf_gaussians* g, const gftorf_frame* frames, int32_t n_frames,
@@ -212,7 +212,7 @@ int gftorf_render_fwd(const gftorf_gaussians* g, const gftorf_frame* frames, int
     if (!out || !out->T_final || !out->n_contrib) return fail(GFTORF_EINVAL, "outputs: T_final and n_contrib are required");
     if (!ws) return fail(GFTORF_EINVAL, "workspace is NULL");
     if (reinterpret_cast<uintptr_t>(ws) % 256) return fail(GFTORF_EINVAL, "workspace must be 256-byte aligned");
-    const gft::Workspace w = gft::carve(ws, g->n, n_frames, P.nf, P.ntx, P.nty, P.cap);
+    const gft::Workspace w = gft::carve(ws, g->n, n_frames, P.nf, P.ntx, P.nty, P.tw * P.th, P.cap);
     if (ws_bytes < w.bytes) return fail(GFTORF_ENOWS, "workspace too small: need " + std::to_string(w.bytes) + " bytes");
     hipStream_t s = static_cast<hipStream_t>(stream);
     (void)hipGetLastError();
@@ -240,7 +240,7 @@ int gftorf_render_bwd(const gftorf_gaussians* g, const gftorf_frame* frames, int
     if (!grad) return fail(GFTORF_EINVAL, "grad is NULL");
     if (!ws) return fail(GFTORF_EINVAL, "workspace is NULL");
     if (reinterpret_cast<uintptr_t>(ws) % 256) return fail(GFTORF_EINVAL, "workspace must be 256-byte aligned");
-    const gft::Workspace w = gft::carve(ws, g->n, n_frames, P.nf, P.ntx, P.nty, P.cap);
+    const gft::Workspace w = gft::carve(ws, g->n, n_frames, P.nf, P.ntx, P.nty, P.tw * P.th, P.cap);
     if (ws_bytes < w.bytes) return fail(GFTORF_ENOWS, "workspace too small: need " + std::to_string(w.bytes) + " bytes");
     hipStream_t s = static_cast<hipStream_t>(stream);
     (void)hipGetLastError();
@@ -310,7 +310,7 @@ int gftorf_copy_lists(const void* ws, int64_t n, int32_t n_frames, const gftorf_
     int rc = build_params(n, n_frames, cfg, &P);
     if (rc) return rc;
     if (!ws) return fail(GFTORF_EINVAL, "workspace is NULL");
-    const gft::Workspace w = gft::carve(const_cast<void*>(ws), n, n_frames, P.nf, P.ntx, P.nty, P.cap);
+    const gft::Workspace w = gft::carve(const_cast<void*>(ws), n, n_frames, P.nf, P.ntx, P.nty, P.tw * P.th, P.cap);
     hipStream_t s = static_cast<hipStream_t>(stream);
     gft::Status st;
     hipError_t e = hipMemcpyAsync(&st, ws, sizeof(st), hipMemcpyDeviceToHost, s);

@@ -240,7 +240,8 @@ __global__ void __launch_bounds__(64 * WPT) k_composite_fwd(Params P, const gfto
                                                             uint8_t* __restrict__ touch,
                                                             const float4* __restrict__ rec,
                                                             const float4* __restrict__ conic,
-                                                            gftorf_outputs out, uint2* __restrict__ wcount) {
+                                                            gftorf_outputs out, uint2* __restrict__ wcount,
+                                                            float* __restrict__ marks, uint32_t n_marks) {
     constexpr int PPT = TW * TH / (64 * WPT);
     static_assert(PPT * 64 * WPT == TW * TH && 64 % U == 0, "whole waves and groups of entries");
     constexpr int RS4 = record_float4s(NF);
@@ -339,6 +340,11 @@ __global__ void __launch_bounds__(64 * WPT) k_composite_fwd(Params P, const gfto
     for (uint32_t pos = 0; pos < len && going; pos += (uint32_t)cnt) {
         cnt = __builtin_amdgcn_readfirstlane((int)min(min(queued, 64u), len - pos));
         if (cnt == 0) break;   // the list is cut at the pair capacity
+        if (pos != 0u && pos / 64u <= n_marks) {   // for the split backward; pos is a multiple of 64
+            float* m = marks + ((size_t)w * n_marks + (pos / 64u - 1u)) * (TW * TH) + p0;
+#pragma unroll
+            for (int i = 0; i < PPT; ++i) m[64 * WPT * i] = T[i];
+        }
         sync();
         {   // stage; past the end: alpha = -1, below every threshold
             const bool have = lane < cnt;
@@ -473,9 +479,9 @@ __global__ void __launch_bounds__(64 * WPT) k_composite_fwd(Params P, const gfto
 
 // Backward: WPT waves per (frame, tile) (1 for large batches; 2 or 4 when
 // the batch has too few tiles to fill the chip), each walking the tile's list
-// for its own pixels; each lane owns PPT pixels of the tile
-// (pixel p = lane + 64 i), so the per-entry cross-lane reduction of the
-// gradient fields is paid once for PPT pixels.
+// for its own pixels; each lane owns PPT pixels of one column (pixel p = lane
+// + 64 (wave + WPT i)), so the per-entry cross-lane reduction of the gradient
+// fields is paid once for PPT pixels.
 //
 // The upstream gradients are constant per pixel, so the recursions of Eq. S2
 // (RGB and depth, factor 1 - alpha) and Eq. S3 (quads, factor (1 - alpha)^2)
@@ -489,13 +495,219 @@ __global__ void __launch_bounds__(64 * WPT) k_composite_fwd(Params P, const gfto
 //   dL/dalpha_k = T_k u_k + T_k^2 v_k - (A1 + 2 A2 + bg) / (1 - alpha_k),
 // so one running sum A = A1 + 2 A2 + bg per pixel suffices:
 //   A <- A + u_k alpha_k T_k + 2 v_k alpha_k T_k^2.
-template <int TW, int TH, int NF, int WPT>
+//
+// SPLIT (batches of few tiles, whose waves would each walk a long list alone):
+// the walk is cut into segments of whole 64-entry batches, a wave each.  The
+// transmittance at a segment's end is the forward's own (marks); the suffix
+// sum A there is the background term and the sums of u_j alpha_j T_j +
+// 2 v_j alpha_j T_j^2 over the segments behind, which k_bwd_segment_sums forms
+// first, walking them front to back: a third more arithmetic for a chain as
+// long as one segment (where the line lies: kept_marks).
+
+// One lane's pixels: constants of the walk and upstream gradients.
+template <int NF, int PPT>
+struct Pixels {
+    float fpx, fpy[PPT];   // centres relative to the tile origin; the lane's pixels share a column
+    uint32_t last[PPT];    // entries of the list up to the pixel's last composited one
+    float gr[PPT][3], gd[PPT], gS[PPT][NF], gC[PPT][NF];
+    float T_end[PPT], bg[PPT];   // final transmittance; background term of A
+    uint32_t walk;         // largest `last` of the wave
+};
+
+template <int TW, int TH, int NF, int WPT, typename Bg>
+__device__ __forceinline__ Pixels<NF, TW * TH / (64 * WPT)> load_pixels(
+    const Params& P, const gftorf_frame& fr, int f, int tx, int ty, int sub, int lane,
+    const float* __restrict__ T_final, const int32_t* __restrict__ n_contrib, const float* __restrict__ d_rgb,
+    const float* __restrict__ d_quad, const float* __restrict__ d_depth, Bg bg_grad) {
+    constexpr int PPT = TW * TH / (64 * WPT);
+    Pixels<NF, PPT> px;
+    const size_t HW = (size_t)P.H * P.W;
+    px.fpx = (float)(lane % TW) + 0.5f;
+    uint32_t walk = 0;
+#pragma unroll
+    for (int i = 0; i < PPT; ++i) {
+        const int pidx = lane + 64 * (sub + WPT * i);
+        const int x = tx * TW + pidx % TW, y = ty * TH + pidx / TW;
+        const bool inside = x < P.W && y < P.H;
+        px.fpy[i] = (float)(pidx / TW) + 0.5f;
+        const size_t pix = (size_t)y * P.W + x;
+        px.T_end[i] = 1.f;
+        px.last[i] = 0;
+        px.gr[i][0] = px.gr[i][1] = px.gr[i][2] = px.gd[i] = px.bg[i] = 0.f;
+#pragma unroll
+        for (int k = 0; k < NF; ++k) px.gS[i][k] = px.gC[i][k] = 0.f;
+        if (inside) {
+            // all loads are issued before any is used: a wave that is alone on
+            // its SIMD would otherwise wait for each
+            const float Tf = T_final[(size_t)f * HW + pix];
+            px.last[i] = (uint32_t)n_contrib[(size_t)f * HW + pix];
+            if (d_rgb)
+                for (int c = 0; c < 3; ++c) px.gr[i][c] = d_rgb[((size_t)f * 3 + c) * HW + pix];
+            if (d_depth) px.gd[i] = d_depth[(size_t)f * HW + pix];
+            float q[NF][GFTORF_MAX_PHASE];
+            if (d_quad)
+#pragma unroll
+                for (int k = 0; k < NF; ++k)
+#pragma unroll
+                    for (int jj = 0; jj < GFTORF_MAX_PHASE; ++jj)
+                        q[k][jj] = d_quad[((size_t)f * P.nq + k * P.nphi + min(jj, P.nphi - 1)) * HW + pix];
+            const float Tp = P.bg_pow == 2 ? Tf * Tf : Tf;
+            float brd = 0.f, bqd = 0.f;
+            for (int c = 0; c < 3; ++c) {
+                brd += fr.bg_rgb[c] * px.gr[i][c];
+                bg_grad(c, px.gr[i][c] * Tf);
+            }
+            if (d_quad)
+#pragma unroll
+                for (int k = 0; k < NF; ++k)
+#pragma unroll
+                    for (int jj = 0; jj < GFTORF_MAX_PHASE; ++jj) {
+                        const int qc = k * P.nphi + jj;
+                        // past the last phase, or a channel the frame does not render
+                        if (jj >= P.nphi || (fr.quad_mask != 0u && !((fr.quad_mask >> qc) & 1u))) continue;
+                        const float g = q[k][jj];
+                        px.gS[i][k] += P.cphi[jj] * g;
+                        px.gC[i][k] += P.sphi[jj] * g;
+                        bqd += fr.bg_quad[qc] * g;
+                        bg_grad(3 + GFTORF_MAX_PHASE * k + jj, g * Tp);
+                    }
+            px.T_end[i] = Tf;
+            px.bg[i] = brd * Tf + (float)P.bg_pow * bqd * Tp;
+        }
+        walk = max(walk, px.last[i]);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) walk = max(walk, (uint32_t)__shfl_xor((int)walk, o, 64));
+    px.walk = (uint32_t)__builtin_amdgcn_readfirstlane((int)walk);
+    return px;
+}
+
+// The segment `seg` of a wave's walk over `walk` list entries: runs of whole
+// 64-entry batches that start at kept marks, as equal as their number allows,
+// the last one to the end of the walk.
+struct Segment {
+    uint32_t n, beg, end;   // segments of the walk; list positions of this one
+};
+
+__device__ __forceinline__ Segment segment_of(uint32_t walk, uint32_t seg, uint32_t n_seg, uint32_t n_marks) {
+    const uint32_t batches = min((walk + 63u) / 64u, n_marks + 1u);
+    const uint32_t per = max(1u, (batches + n_seg - 1u) / n_seg);
+    Segment s;
+    s.n = max(1u, (batches + per - 1u) / per);
+    s.beg = seg * per * 64u;
+    s.end = seg + 1u >= s.n ? walk : (seg + 1u) * per * 64u;
+    return s;
+}
+
+// Wave `b` of a split launch over `items` (tile, part of it) pairs: its item and
+// segment.  Each XCD takes one contiguous eighth of the items, and inside it
+// all first segments come before all second ones: many lists end in the first
+// few, and with an item's segments side by side the round-robin dispatch would
+// give some CUs only empty ones.
+__device__ __forceinline__ bool split_item(uint32_t b, uint32_t items, uint32_t& item, uint32_t& seg) {
+    const uint32_t per = (items + kXcds - 1u) / kXcds, i = b / kXcds;
+    seg = i / per;
+    item = b % kXcds * per + (i - seg * per);
+    return item < items;
+}
+inline unsigned split_grid(int64_t items, int64_t segments) {
+    return (unsigned)((items + kXcds - 1) / kXcds * kXcds * segments);
+}
+
+// The split walk's sums of u_j alpha_j T_j + 2 v_j alpha_j T_j^2 over each
+// segment but the first, front to back from the kept transmittance.
+template <int TW, int TH, int NF, int WPT, int U>
+__global__ void __launch_bounds__(64) k_bwd_segment_sums(
+    Params P, const gftorf_frame* __restrict__ frames, const uint2* __restrict__ ranges,
+    const uint32_t* __restrict__ tval, const float4* __restrict__ rec, const float4* __restrict__ conic,
+    const float* __restrict__ T_final, const int32_t* __restrict__ n_contrib, const float* __restrict__ d_rgb,
+    const float* __restrict__ d_quad, const float* __restrict__ d_depth, const float* __restrict__ marks,
+    float* __restrict__ seg_sums, uint32_t n_seg, uint32_t n_marks) {
+    constexpr int PPT = TW * TH / (64 * WPT);
+    constexpr int RS4 = record_float4s(NF);
+    constexpr int SS4 = staged_float4s(NF);
+    __shared__ float4 srec[SS4][64];
+    uint32_t ws, seg;
+    if (!split_item(blockIdx.x, (uint32_t)(P.F * P.n_tiles * WPT), ws, seg)) return;
+    ++seg;   // the first segment's sum is not needed
+    const int w = (int)ws / WPT, sub = (int)ws - w * WPT;
+    const int f = w / P.n_tiles;
+    const int tile = w - f * P.n_tiles;
+    const int ty = tile / P.ntx, tx = tile - ty * P.ntx;
+    const int lane = threadIdx.x;
+    const uint2 rg = ranges[w];
+    const Pixels<NF, PPT> px = load_pixels<TW, TH, NF, WPT>(P, frames[f], f, tx, ty, sub, lane, T_final, n_contrib,
+                                                            d_rgb, d_quad, d_depth, [](int, float) {});
+    const Segment sg = segment_of(min(px.walk, rg.y - rg.x), seg, n_seg, n_marks);
+    if (seg >= sg.n) return;
+    const float amin = P.alpha_min, amax = P.alpha_max;
+    const float ox = (float)(tx * TW), oy = (float)(ty * TH);
+    float T[PPT], A[PPT];
+    const float* m = marks + ((size_t)w * n_marks + (sg.beg / 64u - 1u)) * (TW * TH) + lane + 64 * sub;
+#pragma unroll
+    for (int i = 0; i < PPT; ++i) T[i] = m[64 * WPT * i], A[i] = 0.f;
+    for (uint32_t lo = sg.beg; lo < sg.end; lo += 64u) {
+        const int cnt = (int)min(64u, sg.end - lo);
+        __syncthreads();
+        if (lane < cnt) {
+            const uint32_t item = tval[rg.x + lo + lane];
+            const float4* r = rec + (size_t)item * RS4;
+            const float4 r0 = r[0];
+            srec[0][lane] = make_float4((r0.x - ox) + r0.z, (r0.y - oy) + r0.w, 0.f, 0.f);
+            srec[1][lane] = conic[item];
+#pragma unroll
+            for (int q = 1; q < RS4; ++q) srec[q + 1][lane] = r[q];
+        }
+        __syncthreads();
+        for (int k0 = 0; k0 < cnt; k0 += U) {
+            // entries past cnt are past every pixel's last: not taken
+            float a[U][PPT];
+#pragma unroll
+            for (int e = 0; e < U; ++e) {
+                const float4 c = srec[0][k0 + e], r1 = srec[1][k0 + e];
+                const SplatCol col = splat_col(c, r1, px.fpx);
+#pragma unroll
+                for (int i = 0; i < PPT; ++i) {
+                    float dy;
+                    a[e][i] = fminf(r1.w * __builtin_amdgcn_exp2f(splat_row(col, c, r1, px.fpy[i], dy)), amax);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < U; ++e) {
+                const float4 r2 = srec[2][k0 + e];
+#pragma unroll
+                for (int i = 0; i < PPT; ++i) {
+                    const uint64_t take = lanes(lo + (uint32_t)(k0 + e) < px.last[i]) & lanes(a[e][i] >= amin);
+                    if (lane_of(take)) {
+                        const float u = px.gr[i][0] * r2.x + px.gr[i][1] * r2.y + px.gr[i][2] * r2.z + px.gd[i] * r2.w;
+                        float v = 0.f;
+#pragma unroll
+                        for (int k = 0; k < NF; ++k) {
+                            const float4 rp = srec[3 + k / 2][k0 + e];
+                            const float t = px.gS[i][k] * ((k & 1) ? rp.z : rp.x) + px.gC[i][k] * ((k & 1) ? rp.w : rp.y);
+                            v = k == 0 ? t : v + t;
+                        }
+                        const float x = T[i] * v;
+                        A[i] += (a[e][i] * T[i]) * ((u + x) + x);
+                        T[i] *= 1.0f - a[e][i];
+                    }
+                }
+            }
+        }
+    }
+    float* o = seg_sums + ((size_t)w * n_seg + seg) * (TW * TH) + lane + 64 * sub;
+#pragma unroll
+    for (int i = 0; i < PPT; ++i) o[64 * WPT * i] = A[i];
+}
+
+template <int TW, int TH, int NF, int WPT, bool SPLIT>
 __global__ void __launch_bounds__(64) k_composite_bwd(
     Params P, const gftorf_frame* __restrict__ frames, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ tval, const float4* __restrict__ rec, const float4* __restrict__ conic,
     const float* __restrict__ T_final, const int32_t* __restrict__ n_contrib,
     const float* __restrict__ d_rgb, const float* __restrict__ d_quad, const float* __restrict__ d_depth,
-    float* __restrict__ grec, float* __restrict__ d_bg) {
+    float* __restrict__ grec, float* __restrict__ d_bg, const float* __restrict__ marks,
+    const float* __restrict__ seg_sums, uint32_t n_seg, uint32_t n_marks) {
     constexpr int PPT = TW * TH / (64 * WPT);   // pixels per lane
     constexpr int B = 64;                      // list entries staged per batch
     constexpr int RS4 = record_float4s(NF);
@@ -505,9 +717,14 @@ __global__ void __launch_bounds__(64) k_composite_bwd(
     __shared__ float4 srec[SS4][B];
     __shared__ uint32_t sitem[B];
 
-    // the WPT waves of a work item are consecutive after the remap: one XCD
-    const int wl = xcd_remap(blockIdx.x, gridDim.x);
-    const int w = wl / WPT, sub = wl - w * WPT;
+    // the waves of a work item are consecutive after the remap: one XCD
+    uint32_t ws, seg = 0u;
+    if constexpr (SPLIT) {
+        if (!split_item(blockIdx.x, (uint32_t)(P.F * P.n_tiles * WPT), ws, seg)) return;
+    } else {
+        ws = (uint32_t)xcd_remap(blockIdx.x, gridDim.x);
+    }
+    const int w = (int)ws / WPT, sub = (int)ws - w * WPT;
     const int f = w / P.n_tiles;
     const int tile = w - f * P.n_tiles;
     const int ty = tile / P.ntx, tx = tile - ty * P.ntx;
@@ -516,76 +733,58 @@ __global__ void __launch_bounds__(64) k_composite_bwd(
     const float amin = P.alpha_min, amax = P.alpha_max;
     const float lamin = amin > 0.f ? __log2f(amin) : -INFINITY;
     const float ox = (float)(tx * TW), oy = (float)(ty * TH);
-    const gftorf_frame& fr = frames[f];
-    const size_t HW = (size_t)P.H * P.W;
 
-    float fpx[PPT], fpy[PPT], T[PPT], A[PPT];
-    uint32_t last[PPT];
-    float gr[PPT][3], gd[PPT], gS[PPT][NF], gC[PPT][NF];
-    float bg_acc[3 + GFTORF_MAX_QUAD];
-    const int nbg = 3 + P.nq;
-    for (int c = 0; c < 3 + GFTORF_MAX_QUAD; ++c) bg_acc[c] = 0.f;
-    uint32_t maxl = 0;
+    float bg_acc[3 + GFTORF_MAX_PHASE * NF];   // colour, then the phases of every frequency
+#pragma unroll
+    for (int c = 0; c < 3 + GFTORF_MAX_PHASE * NF; ++c) bg_acc[c] = 0.f;
+    const Pixels<NF, PPT> px =
+        load_pixels<TW, TH, NF, WPT>(P, frames[f], f, tx, ty, sub, lane, T_final, n_contrib, d_rgb, d_quad, d_depth,
+                                     [&](int c, float v) { bg_acc[c] += v; });
+    // background gradients: dL/dc_bg = sum d_rgb T_final, dL/dq_bg = sum d_quad T_final^p
+    if (d_bg && seg == 0u) {
+#pragma unroll
+        for (int c = 0; c < 3 + GFTORF_MAX_PHASE * NF; ++c) {
+            const int k = (c - 3) / GFTORF_MAX_PHASE, jj = (c - 3) % GFTORF_MAX_PHASE;
+            if (c >= 3 && jj >= P.nphi) continue;
+            const float v = wave_sum(bg_acc[c]);
+            if (lane == 0 && v != 0.f)
+                atomicAdd(&d_bg[(size_t)f * (3 + P.nq) + (c < 3 ? c : 3 + k * P.nphi + jj)], v);
+        }
+    }
+    Segment sg{1u, 0u, min(px.walk, rg.y - rg.x)};
+    if constexpr (SPLIT) {
+        sg = segment_of(sg.end, seg, n_seg, n_marks);
+        if (seg >= sg.n) return;
+    }
+    // the state behind the segment; the suffix sum starts with the background term
+    float T[PPT], A[PPT];
 #pragma unroll
     for (int i = 0; i < PPT; ++i) {
-        const int pidx = lane + 64 * (sub + WPT * i);   // same column for all i
-        const int x = tx * TW + pidx % TW, y = ty * TH + pidx / TW;
-        const bool inside = x < P.W && y < P.H;
-        fpx[i] = (float)(pidx % TW) + 0.5f;   // relative to the tile origin
-        fpy[i] = (float)(pidx / TW) + 0.5f;
-        const size_t pix = (size_t)y * P.W + x;
-        float Tf = 1.f, Tp = 1.f, brd = 0.f, bqd = 0.f;
-        last[i] = 0;
-        gr[i][0] = gr[i][1] = gr[i][2] = gd[i] = 0.f;
-#pragma unroll
-        for (int k = 0; k < NF; ++k) gS[i][k] = gC[i][k] = 0.f;
-        if (inside) {
-            Tf = T_final[(size_t)f * HW + pix];
-            last[i] = (uint32_t)n_contrib[(size_t)f * HW + pix];
-            Tp = P.bg_pow == 2 ? Tf * Tf : Tf;
-            if (d_rgb)
-                for (int c = 0; c < 3; ++c) gr[i][c] = d_rgb[((size_t)f * 3 + c) * HW + pix];
-            if (d_depth) gd[i] = d_depth[(size_t)f * HW + pix];
-            for (int c = 0; c < 3; ++c) {
-                brd += fr.bg_rgb[c] * gr[i][c];
-                bg_acc[c] += gr[i][c] * Tf;
-            }
-            if (d_quad) {
-#pragma unroll
-                for (int k = 0; k < NF; ++k)
-                    for (int jj = 0; jj < P.nphi; ++jj) {
-                        const int qc = k * P.nphi + jj;
-                        if (fr.quad_mask != 0u && !((fr.quad_mask >> qc) & 1u)) continue;   // not rendered
-                        const float g = d_quad[((size_t)f * P.nq + qc) * HW + pix];
-                        gS[i][k] += P.cphi[jj] * g;
-                        gC[i][k] += P.sphi[jj] * g;
-                        bqd += fr.bg_quad[qc] * g;
-                        bg_acc[3 + qc] += g * Tp;
-                    }
-            }
-        }
-        // the suffix sum starts with the background term
-        A[i] = brd * Tf + (float)P.bg_pow * bqd * Tp;
-        T[i] = Tf;
-        maxl = max(maxl, last[i]);
+        T[i] = px.T_end[i];
+        A[i] = px.bg[i];
     }
-    // background gradients: dL/dc_bg = sum d_rgb T_final, dL/dq_bg = sum d_quad T_final^p
-    if (d_bg) {
-        for (int c = 0; c < nbg; ++c) {
-            const float v = wave_sum(bg_acc[c]);
-            if (lane == 0 && v != 0.f) atomicAdd(&d_bg[(size_t)f * nbg + c], v);
+    if constexpr (SPLIT) {
+        const int p0 = lane + 64 * sub;
+        if (seg + 1u < sg.n) {
+            const float* m = marks + ((size_t)w * n_marks + (sg.end / 64u - 1u)) * (TW * TH) + p0;
+#pragma unroll
+            for (int i = 0; i < PPT; ++i) T[i] = m[64 * WPT * i];
+        }
+        for (uint32_t q = sg.n; q-- > seg + 1u;) {
+            const float* m = seg_sums + ((size_t)w * n_seg + q) * (TW * TH) + p0;
+#pragma unroll
+            for (int i = 0; i < PPT; ++i) A[i] += m[64 * WPT * i];
         }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) maxl = max(maxl, (uint32_t)__shfl_xor((int)maxl, o, 64));
     // the record field this lane adds to, and its constant factor: the exponent
     // is in log2 units, and the centre's terms lack -2
     const int fld = field_of_lane<NG>(lane);
     const float LN2 = 0.6931471805599453f;
     const float fscale = fld == 0 || fld == 1 ? -2.0f * LN2 : fld < 5 ? LN2 : 1.0f;
 
-    for (uint32_t hi = min(rg.x + maxl, rg.y); hi > rg.x; ) {
-        const uint32_t lo = (hi - rg.x > (uint32_t)B) ? hi - B : rg.x;
+    const uint32_t first = rg.x + sg.beg;
+    for (uint32_t hi = rg.x + sg.end; hi > first; ) {
+        const uint32_t lo = (hi - first > (uint32_t)B) ? hi - B : first;
         const int cnt = (int)(hi - lo);
         __syncthreads();
         if (lane < cnt) {
@@ -613,11 +812,11 @@ __global__ void __launch_bounds__(64) k_composite_bwd(
             // certain-skip threshold); an entry no pixel takes costs no more
             float dy[PPT], qe[PPT];
             uint64_t pass[PPT], anyp = 0ull;
-            const SplatCol col = splat_col(c, r1, fpx[0]);   // the lane's pixels share a column
+            const SplatCol col = splat_col(c, r1, px.fpx);   // the lane's pixels share a column
 #pragma unroll
             for (int i = 0; i < PPT; ++i) {
-                qe[i] = splat_row(col, c, r1, fpy[i], dy[i]);
-                pass[i] = lanes(kidx < last[i]) & ~lanes(qe[i] < c.z);
+                qe[i] = splat_row(col, c, r1, px.fpy[i], dy[i]);
+                pass[i] = lanes(kidx < px.last[i]) & ~lanes(qe[i] < c.z);
                 anyp |= pass[i];
             }
             if (anyp == 0ull) continue;
@@ -656,24 +855,24 @@ __global__ void __launch_bounds__(64) k_composite_bwd(
                     const float ae = lane_of(act) ? a : 0.0f;
                     const float rom = __builtin_amdgcn_rcpf(1.0f - ae);
                     const float Ti = T[i] * rom;
-                    const float u = gr[i][0] * r2.x + gr[i][1] * r2.y + gr[i][2] * r2.z + gd[i] * r2.w;
-                    float v = gS[i][0] * as[0] + gC[i][0] * ac[0];
+                    const float u = px.gr[i][0] * r2.x + px.gr[i][1] * r2.y + px.gr[i][2] * r2.z + px.gd[i] * r2.w;
+                    float v = px.gS[i][0] * as[0] + px.gC[i][0] * ac[0];
 #pragma unroll
-                    for (int k = 1; k < NF; ++k) v += gS[i][k] * as[k] + gC[i][k] * ac[k];
+                    for (int k = 1; k < NF; ++k) v += px.gS[i][k] * as[k] + px.gC[i][k] * ac[k];
                     const float x = Ti * v, y = u + x;
                     const float dA = Ti * y - rom * A[i];
                     T[i] = Ti;
                     const float w1 = ae * Ti;
                     const float w2 = w1 * Ti;
                     A[i] += w1 * (y + x);
-                    put(g[6], w1 * gr[i][0], i);
-                    put(g[7], w1 * gr[i][1], i);
-                    put(g[8], w1 * gr[i][2], i);
-                    put(g[9], w1 * gd[i], i);
+                    put(g[6], w1 * px.gr[i][0], i);
+                    put(g[7], w1 * px.gr[i][1], i);
+                    put(g[8], w1 * px.gr[i][2], i);
+                    put(g[9], w1 * px.gd[i], i);
 #pragma unroll
                     for (int k = 0; k < NF; ++k) {
-                        put(g[10 + 2 * k], w2 * gS[i][k], i);
-                        put(g[11 + 2 * k], w2 * gC[i][k], i);
+                        put(g[10 + 2 * k], w2 * px.gS[i][k], i);
+                        put(g[11 + 2 * k], w2 * px.gC[i][k], i);
                     }
                     const float aq = decltype(clamps)::value && oG > amax ? 0.0f : ae;
                     const float gq = dA * aq;
@@ -714,7 +913,7 @@ hipError_t fwd_wpt(const Params& P, const gftorf_frame* frames, const Workspace&
     const unsigned blocks = (unsigned)(P.F * P.n_tiles);
 #define GFT_FWD(NF_)                                                                                          \
     hipLaunchKernelGGL((k_composite_fwd<TW, TH, NF_, WPT, U>), dim3(blocks), dim3(64 * WPT), 0, s, P, frames, \
-                       w.ranges, w.granges, w.gval, w.gloc, w.tval, w.touch, w.rec, w.conic, out, w.wcount)
+                       w.ranges, w.granges, w.gval, w.gloc, w.tval, w.touch, w.rec, w.conic, out, w.wcount, w.marks, (uint32_t)kept_marks((int64_t)P.F * P.n_tiles, TW * TH))
     switch (P.nf) {
         case 1: GFT_FWD(1); break;
         case 2: GFT_FWD(2); break;
@@ -731,6 +930,7 @@ hipError_t fwd_wpt(const Params& P, const gftorf_frame* frames, const Workspace&
 // shared).  Measured: 1200 tiles 35.7 against 43.3 us, 4800 tiles 88 us both,
 // 9600 tiles 155 against 142 us.
 constexpr int64_t kFwdTiles = 4096;
+static_assert(kFwdTiles == kSplitTiles, "the split backward needs the forward's 64-entry batches and marks");
 
 template <int TW, int TH>
 hipError_t fwd_nf(const Params& P, const gftorf_frame* frames, const Workspace& w,
@@ -744,14 +944,28 @@ hipError_t fwd_nf(const Params& P, const gftorf_frame* frames, const Workspace& 
     }
 }
 
-template <int TW, int TH, int WPT>
+template <int TW, int TH, int WPT, bool SPLIT>
 hipError_t bwd_wpt(const Params& P, const gftorf_frame* frames, const Workspace& w,
                    const gftorf_outputs& sv, const float* dr, const float* dq, const float* dd,
                    float* dbg, hipStream_t s) {
-    const unsigned blocks = (unsigned)(P.F * P.n_tiles * WPT);
-#define GFT_BWD(NF_)                                                                                  \
-    hipLaunchKernelGGL((k_composite_bwd<TW, TH, NF_, WPT>), dim3(blocks), dim3(64), 0, s, P, frames,     \
-                       w.ranges, w.tval, w.rec, w.conic, sv.T_final, sv.n_contrib, dr, dq, dd, w.grec, dbg)
+    const int64_t tiles = (int64_t)P.F * P.n_tiles;
+    const uint32_t marks = (uint32_t)kept_marks(tiles, TW * TH);
+    const uint32_t segs = SPLIT ? (uint32_t)split_segments(tiles, TW * TH) : 1u;
+    const unsigned waves = (unsigned)(tiles * WPT);
+    constexpr int U = TW * TH / (64 * WPT) == 1 ? 4 : 2;
+#define GFT_BWD(NF_)                                                                                          \
+    if constexpr (SPLIT) {                                                                                    \
+        ProfScope _p("k_bwd_segment_sums", s);                                                                \
+        hipLaunchKernelGGL((k_bwd_segment_sums<TW, TH, NF_, WPT, U>), dim3(split_grid(waves, segs - 1u)), dim3(64), 0, \
+                           s, P, frames, w.ranges, w.tval, w.rec, w.conic, sv.T_final, sv.n_contrib, dr, dq,  \
+                           dd, w.marks, w.seg_sums, segs, marks);                                             \
+    }                                                                                                         \
+    {                                                                                                         \
+        ProfScope _p("k_composite_bwd", s);                                                                   \
+        hipLaunchKernelGGL((k_composite_bwd<TW, TH, NF_, WPT, SPLIT>), dim3(SPLIT ? split_grid(waves, segs) : waves), dim3(64), 0, s, P, \
+                           frames, w.ranges, w.tval, w.rec, w.conic, sv.T_final, sv.n_contrib, dr, dq, dd,    \
+                           w.grec, dbg, w.marks, w.seg_sums, segs, marks);                                    \
+    }
     switch (P.nf) {
         case 1: GFT_BWD(1); break;
         case 2: GFT_BWD(2); break;
@@ -762,24 +976,18 @@ hipError_t bwd_wpt(const Params& P, const gftorf_frame* frames, const Workspace&
     return hipGetLastError();
 }
 
-// Waves per work item of the backward: one while the batch's tiles give at
-// least kBwdWaves waves (several per SIMD, 1024 SIMDs), else 2 (4 below a
-// quarter of that) sharing each tile's list, so a small batch still fills
-// the chip.  Measured on one 640 x 480 frame (1200 tiles): 133 us with one
-// wave per tile, 108 us with two, 107 us with four.
-constexpr int64_t kBwdWaves = 4096;
-
 template <int TW, int TH>
 hipError_t bwd_nf(const Params& P, const gftorf_frame* frames, const Workspace& w,
                   const gftorf_outputs& sv, const float* dr, const float* dq, const float* dd,
                   float* dbg, hipStream_t s) {
-    ProfScope _p("k_composite_bwd", s);
-    const int64_t items = (int64_t)P.F * P.n_tiles;
+    const int64_t tiles = (int64_t)P.F * P.n_tiles;
+    if (kept_marks(tiles, TW * TH) == 0) return bwd_wpt<TW, TH, 1, false>(P, frames, w, sv, dr, dq, dd, dbg, s);
     if constexpr (TW * TH >= 256) {
-        if (items * 4 <= kBwdWaves) return bwd_wpt<TW, TH, 4>(P, frames, w, sv, dr, dq, dd, dbg, s);
-        if (items < kBwdWaves) return bwd_wpt<TW, TH, 2>(P, frames, w, sv, dr, dq, dd, dbg, s);
+        const int wpt = split_waves(tiles, TW * TH);
+        if (wpt == 4) return bwd_wpt<TW, TH, 4, true>(P, frames, w, sv, dr, dq, dd, dbg, s);
+        if (wpt == 2) return bwd_wpt<TW, TH, 2, true>(P, frames, w, sv, dr, dq, dd, dbg, s);
     }
-    return bwd_wpt<TW, TH, 1>(P, frames, w, sv, dr, dq, dd, dbg, s);
+    return bwd_wpt<TW, TH, 1, true>(P, frames, w, sv, dr, dq, dd, dbg, s);
 }
 
 }  // namespace

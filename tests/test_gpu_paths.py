@@ -98,3 +98,25 @@ def test_packed_preprocess_backward(n_frames, sh):
     assert any((v == 0).all(axis=tuple(range(v.ndim - 1))).any() for v in sums.values())   # some have no gradient
     for k, v in sums.items():
         assert_grads_close(res["grads"][k], v, k, rtol=GRAD_RTOL * 1e-2)
+
+
+# the backward of few tiles walks a list in segments of 64-entry batches, as
+# many as there are kept marks (64), the last one to the end: lists of one
+# batch, of a few, one entry into a batch, and past the last mark
+@pytest.mark.parametrize("tile", [(8, 8), (16, 16), (32, 8)])
+@pytest.mark.parametrize("n", [40, 64, 65, 400, 4300])
+def test_split_backward_walk(n, tile):
+    wl = scenes.tiny_scene(n, 37, 19, seed=n, log_scale_mean=float(np.log(0.6)))
+    rng = np.random.default_rng(n)
+    # faint, so that no pixel stops before the end of its list
+    wl.gaussians.opacity_logit[:] = rng.uniform(-5.2, -4.5 if n > 1000 else -1.0, n).astype(np.float32)
+    cfg = dataclasses.replace(wl.cfg, tile_w=tile[0], tile_h=tile[1], T_min=0.0)
+    frames = scenes.identity_frames([0.0], 37, 19, wl.frames[0].fx, wl.frames[0].fy, 4, bg_seed=1)
+    base = oref.render(wl.gaussians, frames, cfg)
+    up = mask_upstream(scenes.upstream_grads(1, cfg, seed=5), ~base["flagged"])
+    ref = oref.render(wl.gaussians, frames, cfg, upstream=up)
+    res = run_gpu(wl.gaussians, frames, cfg, upstream=up, want_bg=True)
+    assert res["n_contrib"].max() > 0.5 * n
+    for k in ("mean", "scale", "quat", "opacity_logit", "rgb", "albedo"):
+        assert_grads_close(res["grads"][k], ref["grads"][k], k)
+    assert_grads_close(res["grad_bg"], np.concatenate([ref["grad_bg_rgb"], ref["grad_bg_quad"]], 1), "bg")
