@@ -50,6 +50,21 @@ __device__ __forceinline__ Groups groups_of(const Params& P) {
     return g;
 }
 
+// The depth-sorted items: in buffer 1, or in buffer 0 where the sort needed
+// its fourth pass.
+struct DepthOrder {
+    const uint32_t *key0, *key1, *item0, *item1;
+    const uint2 *rect0, *rect1;
+    const uint32_t* flag;
+    __device__ __forceinline__ bool wide() const { return *flag != 0u; }
+    __device__ __forceinline__ const uint32_t* keys(bool w) const { return w ? key0 : key1; }
+    __device__ __forceinline__ const uint32_t* items(bool w) const { return w ? item0 : item1; }
+    __device__ __forceinline__ const uint2* rects(bool w) const { return w ? rect0 : rect1; }
+};
+DepthOrder depth_order(const Workspace& w) {
+    return {w.dkey[0], w.dkey[1], w.dval[0], w.dval[1], w.drect[0], w.drect[1], w.sctl + kSortWide};
+}
+
 // ---- level A: items -> groups ----------------------------------------------
 
 // Group counts of each chunk of C items: one workgroup of 256 threads per CPW
@@ -58,14 +73,16 @@ __device__ __forceinline__ Groups groups_of(const Params& P) {
 constexpr int kMaxChunksPerBlock = 4;
 
 __global__ void __launch_bounds__(256) k_group_count(Params P, int C, int QC, int CPW,
-                                                     const uint32_t* __restrict__ dkey,
-                                                     const uint2* __restrict__ drect,
+                                                     DepthOrder order,
                                                      uint32_t* __restrict__ cntA, uint32_t* __restrict__ touch) {
     // no item has been walked yet (the flags' bytes, four at a time; the
     // workspace pads them to whole words)
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < (P.n * P.F + 3) / 4; i += (int64_t)gridDim.x * 256)
         touch[i] = 0u;
     __shared__ uint32_t lcnt[kMaxChunksPerBlock][kMaxGroupsPerFrame];
+    const bool wide = order.wide();
+    const uint32_t* dkey = order.keys(wide);
+    const uint2* drect = order.rects(wide);
     const Groups G = groups_of(P);
     const int TPC = 256 / CPW;   // threads per chunk
     const int sub = (int)threadIdx.x / TPC, lt = (int)threadIdx.x - sub * TPC;
@@ -288,15 +305,16 @@ __device__ __forceinline__ void place_group_row(const Groups& G, long long beg, 
 
 template <int NB>
 __global__ void __launch_bounds__(64) k_group_place(Params P, int C, int QC, int RA,
-                                                         const uint32_t* __restrict__ dval,
-                                                         const uint32_t* __restrict__ dkey,
-                                                         const uint2* __restrict__ drect,
+                                                         DepthOrder order,
                                                          const uint32_t* __restrict__ cntA,
                                                          const uint2* __restrict__ granges,
                                                          uint32_t* __restrict__ gval,
                                                          uint16_t* __restrict__ gloc) {
     extern __shared__ uint32_t cursor[];   // [ngx] list cursors of the work item's group row
     const Groups G = groups_of(P);
+    const bool wide = order.wide();
+    const uint32_t *dkey = order.keys(wide), *dval = order.items(wide);
+    const uint2* drect = order.rects(wide);
     const int lane = threadIdx.x;
     const uint32_t cap = (uint32_t)(P.cap < 0xffffffffull ? P.cap : 0xffffffffull);
     const uint32_t nrun = ((uint32_t)QC + (uint32_t)RA - 1) / (uint32_t)RA;   // runs of RA chunks per frame
@@ -559,7 +577,7 @@ BinGeom bin_geometry(int64_t n, int32_t n_frames, int ntx, int nty, uint64_t cap
 constexpr int64_t kPlaceGridA = 131072;
 constexpr int64_t kCountGrid = 8192;
 
-hipError_t launch_binning(const Params& P, const Workspace& w, int dbuf, hipStream_t s) {
+hipError_t launch_binning(const Params& P, const Workspace& w, hipStream_t s) {
     const BinGeom g = bin_geometry(P.n, P.F, P.ntx, P.nty, P.cap);
     const int K = P.F * g.ng;
     const unsigned chunks = (unsigned)(P.F * g.QC);
@@ -567,7 +585,7 @@ hipError_t launch_binning(const Params& P, const Workspace& w, int dbuf, hipStre
         ProfScope _p("k_group_count", s);
         const int cpw = g.C >= 512 ? 1 : (g.C >= 256 ? 2 : 4);   // 512 / C in [1, 4]
         hipLaunchKernelGGL(k_group_count, dim3((chunks + cpw - 1) / cpw), dim3(256), 0, s, P, g.C, g.QC, cpw,
-                           w.dkey[dbuf], w.drect[dbuf], w.cntA, reinterpret_cast<uint32_t*>(w.touch));
+                           depth_order(w), w.cntA, reinterpret_cast<uint32_t*>(w.touch));
     }
     if (chunks) {
         ProfScope _p("k_group_colscan", s);
@@ -594,10 +612,10 @@ hipError_t launch_binning(const Params& P, const Workspace& w, int dbuf, hipStre
         const unsigned grid = (unsigned)((items < kPlaceGridA ? items : kPlaceGridA) + 7) / 8 * 8;
         if ((int64_t)RA * g.C >= 1024)
             hipLaunchKernelGGL(k_group_place<8>, dim3(grid), dim3(64), 4 * (size_t)ngx, s, P, g.C, g.QC, RA,
-                               w.dval[dbuf], w.dkey[dbuf], w.drect[dbuf], w.cntA, w.granges, w.gval, w.gloc);
+                               depth_order(w), w.cntA, w.granges, w.gval, w.gloc);
         else
             hipLaunchKernelGGL(k_group_place<1>, dim3(grid), dim3(64), 4 * (size_t)ngx, s, P, g.C, g.QC, RA,
-                               w.dval[dbuf], w.dkey[dbuf], w.drect[dbuf], w.cntA, w.granges, w.gval, w.gloc);
+                               depth_order(w), w.cntA, w.granges, w.gval, w.gloc);
     }
     // persistent counting grid: every wave takes a run of segments
     const int64_t runs = (g.max_segments + kCountRun - 1) / kCountRun;
@@ -618,11 +636,11 @@ hipError_t launch_binning(const Params& P, const Workspace& w, int dbuf, hipStre
     return hipGetLastError();
 }
 
-void launch_item_rects(const Workspace& w, int dbuf, uint2* out, hipStream_t s) {
+void launch_item_rects(const Workspace& w, uint2* out, hipStream_t s) {
     if (w.M == 0) return;
     const long long blocks = (w.M + 255) / 256;
     hipLaunchKernelGGL(k_item_rects, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0, s,
-                       w.dval[dbuf], w.drect[dbuf], (long long)w.M, out);
+                       w.dval[1], w.drect[1], (long long)w.M, out);
 }
 
 void launch_tile_lists(const Params& P, const Workspace& w, hipStream_t s) {

@@ -17,6 +17,19 @@ __device__ __forceinline__ T wave_inclusive_scan(T x) {
     return x;
 }
 
+// 32-bit integers: row shifts and row broadcasts of the lanes (DPP) in place
+// of six trips through LDS.
+template <>
+__device__ __forceinline__ uint32_t wave_inclusive_scan<uint32_t>(uint32_t x) {
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);   // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);   // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);   // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);   // row_shr:8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);   // row_bcast:15, rows 1 and 3
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);   // row_bcast:31, rows 2 and 3
+    return x;
+}
+
 template <typename T>
 __device__ __forceinline__ T wave_reduce_sum(T x) {
 #pragma unroll
@@ -25,7 +38,7 @@ __device__ __forceinline__ T wave_reduce_sum(T x) {
 }
 
 // Exclusive scan over a workgroup of NT threads (NT multiple of 64, <= 1024).
-// `scratch` must hold NT/64 + 1 elements of T.  Returns the exclusive prefix
+// `scratch` must hold NT/64 elements of T.  Returns the exclusive prefix
 // of the calling thread; *total receives the workgroup sum.  Contains
 // barriers: every thread of the workgroup must call it.
 template <typename T, int NT>
@@ -36,20 +49,16 @@ __device__ __forceinline__ T block_exclusive_scan(T x, T* scratch, T* total) {
     T inc = wave_inclusive_scan(x);
     if (lane == 63) scratch[wave] = inc;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        T run = 0;
-        for (int w = 0; w < NW; ++w) {
-            T v = scratch[w];
-            scratch[w] = run;
-            run += v;
-        }
-        scratch[NW] = run;
+    T before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const T v = scratch[w];
+        before += w < wave ? v : T(0);
+        all += v;
     }
+    *total = all;
     __syncthreads();
-    T res = scratch[wave] + inc - x;
-    *total = scratch[NW];
-    __syncthreads();
-    return res;
+    return before + inc - x;
 }
 
 }  // namespace gft

@@ -88,7 +88,6 @@ int build_params(int64_t n, int32_t F, const gftorf_config* c, gft::Params* P) {
 }
 
 // Buffer holding the depth-sorted items after the forward.
-int depth_buffer(const gft::Params& P) { return gft::depth_sort_passes(P.F) & 1; }
 
 int check_gauss(const gftorf_gaussians* g) {
     if (!g) return fail(GFTORF_EINVAL, "gaussians is NULL");
@@ -219,8 +218,8 @@ int gftorf_render_fwd(const gftorf_gaussians* g, const gftorf_frame* frames, int
 
     // every Status field is written during the forward (no clearing launch)
     gft::launch_preprocess(P, *g, frames, w, s);
-    const int dbuf = gft::launch_depth_sort(P, w, s);
-    hipError_t e = gft::launch_binning(P, w, dbuf, s);
+    gft::launch_depth_sort(P, w, s);
+    hipError_t e = gft::launch_binning(P, w, s);
     if (e == hipSuccess) e = gft::launch_composite_fwd(P, frames, w, *out, s);
     if (e == hipSuccess) e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "gftorf_render_fwd");
@@ -318,7 +317,7 @@ int gftorf_copy_lists(const void* ws, int64_t n, int32_t n_frames, const gftorf_
     if (e != hipSuccess) return hip_fail(e, "gftorf_copy_lists");
     unsigned long long np = st.n_pairs < P.cap ? st.n_pairs : P.cap;
     if (pair_capacity >= 0 && np > (unsigned long long)pair_capacity) np = (unsigned long long)pair_capacity;
-    const int db = depth_buffer(P);
+    if (depth_key || depth_item || item_rect) gft::launch_sort_settle(w, s);
     auto cp = [&](void* dst, const void* src, size_t bytes) {
         if (dst && bytes && e == hipSuccess) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, s);
     };
@@ -331,11 +330,11 @@ int gftorf_copy_lists(const void* ws, int64_t n, int32_t n_frames, const gftorf_
         e = hipGetLastError();
     }
     cp(pair_item, w.tval, 4 * np);
-    cp(depth_key, w.dkey[db], 4 * (size_t)w.M);
-    cp(depth_item, w.dval[db], 4 * (size_t)w.M);
+    cp(depth_key, w.dkey[1], 4 * (size_t)w.M);
+    cp(depth_item, w.dval[1], 4 * (size_t)w.M);
     cp(item_count, w.cnt, 4 * (size_t)w.M);
     if (item_rect && e == hipSuccess) {
-        gft::launch_item_rects(w, db, reinterpret_cast<uint2*>(item_rect), s);
+        gft::launch_item_rects(w, reinterpret_cast<uint2*>(item_rect), s);
         e = hipGetLastError();
     }
     cp(tile_ranges, w.ranges, 8 * (size_t)P.F * P.n_tiles);

@@ -11,21 +11,30 @@ namespace gft {
 constexpr double kSpeedOfLight = 299792458.0;   // m/s
 constexpr float kLog2e = 1.4426950408889634f;
 
-// Radix sort geometry: 256 threads (4 wave64), 8 keys per thread.
+// Depth sort geometry: 8 keys per thread; tiles of 2048 keys (256 threads)
+// where each pass is one launch, of 4096 (512 threads) elsewhere, so that a
+// tile's run of one digit stays 8 keys long.
 constexpr uint32_t kCulledKey = 0xffffffffu;   // depth key of a culled item
-constexpr int kSortThreads = 256;
+constexpr int kSortThreads = 256, kBigThreads = 512;
 constexpr int kSortItems = 8;
-constexpr int kSortTile = kSortThreads * kSortItems;   // 2048 keys per tile
-constexpr int kSortBuckets = 256;                       // <= 8 digit bits per pass
-constexpr int kSortPasses = 4;                          // 32-bit keys
+constexpr int kDigitBits = 9;
+constexpr int kSortBuckets = 1 << kDigitBits;
+constexpr int kSortPasses = 3;                              // passes every batch needs
+constexpr int kSortWideShift = kDigitBits * kSortPasses;    // bits past these: one more pass
 // Batches of at most this many sort tiles (all frames) sort with one launch
 // per pass (decoupled look-back over the frame's earlier tiles) after one
-// histogram launch; larger batches use three launches per pass.
+// histogram launch; larger batches use three launches per pass, whose tiles
+// need not wait for each other (a pass over 4 frames of 100k, 196 tiles: 458
+// us with one launch per sort pass, 467 with three; 8 frames of 200k, 784
+// tiles: 714 with one, 677 with three).
 constexpr int64_t kOneSweepMaxTiles = 256;
-// Words of the one-sweep control block: the next tile of each pass, then the
-// flag set when a look-back wait gave up.
+// Words of the sort's control block: the next tile of each one-sweep pass,
+// the flag set when a look-back wait gave up, and the flag set when some valid
+// depth needed the last pass.  The sorted items are then in buffer 0, else in
+// buffer 1.
 constexpr int kSortCtlWords = 8;
-constexpr int kSortFault = kSortPasses;
+constexpr int kSortFault = kSortPasses + 1;
+constexpr int kSortWide = kSortPasses + 2;
 
 // Tile binning works on chunks of depth-sorted items of one frame, first into
 // groups of 8x8 tiles (one LDS counter per group of a frame), then into tiles.
@@ -127,12 +136,11 @@ struct Workspace {
     uint32_t* dkey[2];      // [M] depth keys (double buffer)
     uint32_t* dval[2];      // [M] item ids
     uint2* drect[2];        // [M] tile rectangles (x_lo | x_hi << 16, y_lo | y_hi << 16), sort payload
-    uint32_t* counts;       // [F][256][max_sort_tiles] per-tile digit counts of the depth sort
-    uint32_t* totals;       // [F][256] digit totals per frame
-    uint32_t* sctl;         // [kSortCtlWords + F * kSortPasses * 256] one-sweep control words,
-                            // then the digit counts of every frame and pass (shist)
-    uint32_t* shist;        // = sctl + kSortCtlWords
-    uint32_t* slook[2];     // [F * max_sort_tiles][256] look-back words (one-sweep batches only)
+    uint32_t* counts;       // [F][max_sort_tiles][kSortBuckets] per-tile digit counts of the depth sort
+    uint32_t* totals;       // [F][kSortBuckets] digit totals per frame
+    uint32_t* sctl;         // [kSortCtlWords] control words, in one-sweep batches followed by
+    uint32_t* shist;        // [F][kSortPasses + 1][kSortBuckets] digit counts of every frame and pass
+    uint32_t* slook[2];     // [F * max_sort_tiles][kSortBuckets] look-back words (one-sweep batches only)
     uint32_t* cntA;         // [F][QC][ng] per-chunk group counts, then column prefixes
     uint32_t* lenA;         // [F * ng] group-list lengths
     uint2* granges;         // [F * ng] group-list ranges in gval
@@ -147,7 +155,8 @@ struct Workspace {
     float* marks;           // [F * n_tiles][kept_marks][tile pixels] transmittance at list positions 64, 128, ..
     float* seg_sums;        // [F * n_tiles][split_segments][tile pixels] suffix-sum terms per segment
     int64_t M;
-    int64_t max_sort_tiles;
+    bool one_sweep;         // the depth sort's passes are one launch each
+    int64_t max_sort_tiles; // sort tiles per frame
     size_t bytes;
 };
 
@@ -165,8 +174,9 @@ inline Workspace carve(void* base, int64_t n, int32_t F, int nf, int ntx, int nt
     const int64_t M = n * F;
     const BinGeom g = bin_geometry(n, F, ntx, nty, cap);
     w.M = M;
-    w.max_sort_tiles = (n + kSortTile - 1) / kSortTile;   // sort tiles per frame
-    if (w.max_sort_tiles < 1) w.max_sort_tiles = 1;
+    const int64_t small_tile = kSortThreads * kSortItems, big_tile = kBigThreads * kSortItems;
+    w.one_sweep = F * ((n + small_tile - 1) / small_tile) <= kOneSweepMaxTiles;
+    w.max_sort_tiles = w.one_sweep ? (n + small_tile - 1) / small_tile : (n + big_tile - 1) / big_tile;
     const int64_t K = (int64_t)F * n_tiles;
     w.status = reinterpret_cast<Status*>(take(sizeof(Status)));
     w.rec = reinterpret_cast<float4*>(take(sizeof(float4) * record_float4s(nf) * M));
@@ -177,13 +187,13 @@ inline Workspace carve(void* base, int64_t n, int32_t F, int nf, int ntx, int nt
     for (int i = 0; i < 2; ++i) w.dkey[i] = reinterpret_cast<uint32_t*>(take(4 * M));
     for (int i = 0; i < 2; ++i) w.dval[i] = reinterpret_cast<uint32_t*>(take(4 * M));
     for (int i = 0; i < 2; ++i) w.drect[i] = reinterpret_cast<uint2*>(take(sizeof(uint2) * M));
-    w.counts = reinterpret_cast<uint32_t*>(take(4 * (size_t)F * kSortBuckets * w.max_sort_tiles));
+    const size_t sort_words = (size_t)F * w.max_sort_tiles * kSortBuckets;
+    w.counts = reinterpret_cast<uint32_t*>(take(w.one_sweep ? 0 : 4 * sort_words));
     w.totals = reinterpret_cast<uint32_t*>(take(4 * (size_t)F * kSortBuckets));
-    w.sctl = reinterpret_cast<uint32_t*>(take(4 * ((size_t)kSortCtlWords + (size_t)F * kSortPasses * kSortBuckets)));
+    w.sctl = reinterpret_cast<uint32_t*>(
+        take(4 * (kSortCtlWords + (w.one_sweep ? (size_t)F * (kSortPasses + 1) * kSortBuckets : 0))));
     w.shist = w.sctl ? w.sctl + kSortCtlWords : nullptr;
-    const int64_t sort_tiles = (int64_t)F * w.max_sort_tiles;
-    const size_t look_words = sort_tiles <= kOneSweepMaxTiles ? (size_t)sort_tiles * kSortBuckets : 0;
-    for (int i = 0; i < 2; ++i) w.slook[i] = reinterpret_cast<uint32_t*>(take(4 * look_words));
+    for (int i = 0; i < 2; ++i) w.slook[i] = reinterpret_cast<uint32_t*>(take(w.one_sweep ? 4 * sort_words : 0));
     const int64_t KG = (int64_t)F * g.ng;
     w.cntA = reinterpret_cast<uint32_t*>(take(4 * (size_t)F * g.QC * g.ng));
     w.lenA = reinterpret_cast<uint32_t*>(take(4 * KG));
@@ -229,16 +239,14 @@ struct ProfScope {
 // ---- host-side launchers (defined in the .hip files) -----------------------
 void launch_preprocess(const Params& P, const gftorf_gaussians& g, const gftorf_frame* frames,
                        const Workspace& w, hipStream_t s);
-int depth_sort_passes(int n_frames);
-int launch_depth_sort(const Params& P, const Workspace& w, hipStream_t s);
+void launch_depth_sort(const Params& P, const Workspace& w, hipStream_t s);
+void launch_sort_settle(const Workspace& w, hipStream_t s);   // sorted items to buffer 1
 // True when this batch sorts with one launch per pass (its few sort tiles
-// make the look-back chains short); the preprocess then clears the sort's
-// control words and digit counts.
-inline bool one_sweep_sort(const Params& P, const Workspace& w) {
-    return w.M > 0 && (int64_t)P.F * w.max_sort_tiles <= kOneSweepMaxTiles;
-}
-hipError_t launch_binning(const Params& P, const Workspace& w, int dbuf, hipStream_t s);
-void launch_item_rects(const Workspace& w, int dbuf, uint2* out, hipStream_t s);
+// make the look-back chains short); the preprocess then also clears the
+// sort's digit counts, not its control words alone.
+inline bool one_sweep_sort(const Params&, const Workspace& w) { return w.M > 0 && w.one_sweep; }
+hipError_t launch_binning(const Params& P, const Workspace& w, hipStream_t s);
+void launch_item_rects(const Workspace& w, uint2* out, hipStream_t s);
 void launch_tile_lists(const Params& P, const Workspace& w, hipStream_t s);   // completes every tile list
 void launch_keys_from_ranges(const Params& P, const Workspace& w, uint32_t* keys,
                              unsigned long long limit, hipStream_t s);

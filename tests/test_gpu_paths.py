@@ -120,3 +120,29 @@ def test_split_backward_walk(n, tile):
     for k in ("mean", "scale", "quat", "opacity_logit", "rgb", "albedo"):
         assert_grads_close(res["grads"][k], ref["grads"][k], k)
     assert_grads_close(res["grad_bg"], np.concatenate([ref["grad_bg_rgb"], ref["grad_bg_quad"]], 1), "bg")
+
+
+# depths over more than the 16 octaves past near_z that three sort passes
+# resolve, in the one-launch and the three-launch passes: the fourth pass runs
+# and its result is the one that is read
+@pytest.mark.parametrize("n,F", [(1, 1), (5000, 2), (2048 * 128 + 5, 2)])
+@pytest.mark.parametrize("near,far", [(1e-6, 1.0), (0.0, 1.0), (0.2, 1e5), (0.2, 2.0 ** 14)])
+def test_depth_sort_wide_range(n, F, near, far):
+    W, H = 96, 72
+    g = scenes.draw_gaussians(n, W, H, 80.0, 80.0, seed=41)
+    rng = np.random.default_rng(42)
+    move = rng.random(n) < 0.3
+    s = np.where(move, far, 1.0)
+    g.mean[:] = (g.mean * s).astype(np.float32)
+    g.mean[2, ::7] = np.float32(-1.0)   # culled
+    frames = scenes.identity_frames([0.1 * f for f in range(F)], W, H, 80.0, 80.0, 4)
+    cfg = dataclasses.replace(scenes.RenderConfig(width=W, height=H), near_z=near)
+    res = run_gpu(g, frames, cfg, channels=("rgb",))
+    lists = gpu_lists(res, g, frames, cfg, pairs_to_host=n < 10000)
+    key = np.concatenate([obin.project(g, fr, cfg, f)["key"] for f, fr in enumerate(frames)]).astype(np.int64)
+    want = np.concatenate([f * n + np.argsort(key[f * n:(f + 1) * n], kind="stable") for f in range(F)])
+    np.testing.assert_array_equal(lists["depth_item"].astype(np.int64), want)
+    np.testing.assert_array_equal(lists["depth_key"].astype(np.int64), key[want])
+    if n < 10000:
+        pairs = obin.sorted_pairs(g, frames, cfg)
+        assert np.array_equal(lists["pair_item"], (pairs["frame"] * n + pairs["index"]).astype(np.uint32))
