@@ -28,6 +28,10 @@ constexpr int kSortWideShift = kDigitBits * kSortPasses;    // bits past these: 
 // us with one launch per sort pass, 467 with three; 8 frames of 200k, 784
 // tiles: 714 with one, 677 with three).
 constexpr int64_t kOneSweepMaxTiles = 256;
+// Frames of at most this many items are each sorted by one workgroup in one
+// launch (forward pass over one frame, with and without: 2000 items 57 and 75
+// us, 4096 79 and 95, 8192 114 and 119, 12000 135 and 125).
+constexpr int64_t kFrameSortMax = 8192;
 // Words of the sort's control block: the next tile of each one-sweep pass,
 // the flag set when a look-back wait gave up, and the flag set when some valid
 // depth needed the last pass.  The sorted items are then in buffer 0, else in
@@ -155,7 +159,7 @@ struct Workspace {
     float* marks;           // [F * n_tiles][kept_marks][tile pixels] transmittance at list positions 64, 128, ..
     float* seg_sums;        // [F * n_tiles][split_segments][tile pixels] suffix-sum terms per segment
     int64_t M;
-    bool one_sweep;         // the depth sort's passes are one launch each
+    bool one_sweep;         // the depth sort's passes are one launch each (frames past kFrameSortMax)
     int64_t max_sort_tiles; // sort tiles per frame
     size_t bytes;
 };
@@ -175,7 +179,7 @@ inline Workspace carve(void* base, int64_t n, int32_t F, int nf, int ntx, int nt
     const BinGeom g = bin_geometry(n, F, ntx, nty, cap);
     w.M = M;
     const int64_t small_tile = kSortThreads * kSortItems, big_tile = kBigThreads * kSortItems;
-    w.one_sweep = F * ((n + small_tile - 1) / small_tile) <= kOneSweepMaxTiles;
+    w.one_sweep = n > kFrameSortMax && F * ((n + small_tile - 1) / small_tile) <= kOneSweepMaxTiles;
     w.max_sort_tiles = w.one_sweep ? (n + small_tile - 1) / small_tile : (n + big_tile - 1) / big_tile;
     const int64_t K = (int64_t)F * n_tiles;
     w.status = reinterpret_cast<Status*>(take(sizeof(Status)));
@@ -188,7 +192,7 @@ inline Workspace carve(void* base, int64_t n, int32_t F, int nf, int ntx, int nt
     for (int i = 0; i < 2; ++i) w.dval[i] = reinterpret_cast<uint32_t*>(take(4 * M));
     for (int i = 0; i < 2; ++i) w.drect[i] = reinterpret_cast<uint2*>(take(sizeof(uint2) * M));
     const size_t sort_words = (size_t)F * w.max_sort_tiles * kSortBuckets;
-    w.counts = reinterpret_cast<uint32_t*>(take(w.one_sweep ? 0 : 4 * sort_words));
+    w.counts = reinterpret_cast<uint32_t*>(take(w.one_sweep || n <= kFrameSortMax ? 0 : 4 * sort_words));
     w.totals = reinterpret_cast<uint32_t*>(take(4 * (size_t)F * kSortBuckets));
     w.sctl = reinterpret_cast<uint32_t*>(
         take(4 * (kSortCtlWords + (w.one_sweep ? (size_t)F * (kSortPasses + 1) * kSortBuckets : 0))));

@@ -25,7 +25,8 @@
 // sort tile from an atomic counter, ranks its keys, publishes its per-digit
 // counts and adds those of the frame's earlier tiles by decoupled look-back
 // (a bounded wait: those tiles were taken earlier, so their workgroups are
-// running), then scatters.  Sort tiles never straddle a frame.  Each item's
+// running), then scatters.  Small frames are each sorted by one workgroup in
+// LDS.  Sort tiles never straddle a frame.  Each item's
 // tile rectangle rides along as payload, so the binning kernels read it in
 // depth order without gathering it by item id; the item id itself is first
 // written by the first pass (it is the position there).  Ranking inside a
@@ -541,6 +542,91 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_onesweep(
     T.scatter(S, st, at, valid, wave, shift, base, n, kout, vout, rout);
 }
 
+// Frames of at most kFrameSortMax items: one workgroup sorts a frame in LDS,
+// all passes in one launch, and writes the result to buffer 1.  IT keys per
+// thread.  Bound by its chain of barriers and LDS round trips, which is still
+// shorter than that of five launches up to kFrameSortMax items.
+constexpr int kFrameThreads = 1024;
+template <int IT>
+__global__ void __launch_bounds__(kFrameThreads) k_sort_frame(const uint32_t* __restrict__ kin,
+                                                              const uint2* __restrict__ rin, uint32_t n, uint32_t base,
+                                                              uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
+                                                              uint2* __restrict__ rout) {
+    constexpr int WAVES = kFrameThreads / 64;
+    static_assert(IT * kFrameThreads <= 65536, "positions in 16 bits");
+    __shared__ uint2 pair[IT * kFrameThreads];
+    __shared__ uint16_t cnt[WAVES][kSortBuckets];
+    __shared__ uint32_t scratch[WAVES];
+    const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
+    const size_t first = (size_t)blockIdx.x * n;
+    const uint32_t at = wave * (64 * IT) + lane;
+    uint32_t k[IT], v[IT], rank[IT];
+    bool wide = false;
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        v[it] = at + 64 * it;
+        k[it] = v[it] < n ? kin[first + v[it]] : kCulledKey;
+        wide |= key_wide(k[it], base);
+    }
+    const int passes = __syncthreads_or(wide) ? kSortPasses + 1 : kSortPasses;
+    volatile __attribute__((address_space(3))) uint16_t* wc =
+        (volatile __attribute__((address_space(3))) uint16_t*)cnt[wave];
+    for (int pass = 0; pass < passes; ++pass) {
+        const int shift = kDigitBits * pass;
+        for (int i = lane; i < kSortBuckets / 2; i += 64) reinterpret_cast<uint32_t*>(cnt[wave])[i] = 0u;
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {   // the ranking of TileSort
+            const bool valid = at + 64 * it < n;
+            const uint32_t d = key_digits(k[it], base) >> shift & (kSortBuckets - 1);
+            const uint64_t peers = peers_of<kDigitBits>(d, __builtin_amdgcn_ballot_w64(valid));
+            const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32),
+                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
+            const uint32_t c = (uint32_t)__popcll(peers);
+            uint32_t prev = 0;
+            if (valid) prev = wc[d];
+            if (valid && below == c - 1) wc[d] = (uint16_t)(prev + c);
+            rank[it] = prev + below;
+        }
+        __syncthreads();
+        uint32_t c[WAVES], all = 0, tot;
+        if (tid < kSortBuckets)
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) {
+                c[w] = cnt[w][tid];
+                all += c[w];
+            }
+        uint32_t run = block_exclusive_scan<uint32_t, kFrameThreads>(all, scratch, &tot);
+        if (tid < kSortBuckets)
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) {
+                cnt[w][tid] = (uint16_t)run;
+                run += c[w];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const uint32_t d = key_digits(k[it], base) >> shift & (kSortBuckets - 1);
+            if (at + 64 * it < n) pair[wc[d] + rank[it]] = make_uint2(k[it], v[it]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const uint2 p = pair[at + 64 * it];   // past n: never written, never used
+            k[it] = p.x;
+            v[it] = p.y;
+        }
+    }
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const uint32_t j = at + 64 * it;
+        if (j < n) {
+            kout[first + j] = k[it];
+            vout[first + j] = (uint32_t)first + v[it];
+            rout[first + j] = rin[first + v[it]];
+        }
+    }
+}
+
 // Introspection: a result that the fourth pass left in buffer 0, to buffer 1.
 __global__ void k_sort_settle(const uint32_t* __restrict__ sctl, long long M, const uint32_t* __restrict__ k0,
                               const uint32_t* __restrict__ v0, const uint2* __restrict__ r0,
@@ -628,6 +714,18 @@ void launch_fill_f32(float* p, float v, int64_t n, hipStream_t s) {
 void launch_depth_sort(const Params& P, const Workspace& w, hipStream_t s) {
     if (w.M == 0) return;
     int cur = 0;
+    if (P.n <= kFrameSortMax) {
+        static_assert(kFrameSortMax == 8 * kFrameThreads, "the largest frame a workgroup sorts");
+        ProfScope _p("k_sort_frame", s);
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(P.F), dim3(kFrameThreads), 0, s, w.dkey[0], w.drect[0], (uint32_t)P.n,
+                               key_base(P), w.dkey[1], w.dval[1], w.drect[1]);
+        };
+        if (P.n <= 2 * kFrameThreads) go(k_sort_frame<2>);
+        else if (P.n <= 4 * kFrameThreads) go(k_sort_frame<4>);
+        else go(k_sort_frame<8>);
+        return;
+    }
     // the preprocess has cleared the control words (and shist for one sweep)
     if (one_sweep_sort(P, w)) {
         const long long tpf = w.max_sort_tiles;

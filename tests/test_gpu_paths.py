@@ -146,3 +146,30 @@ def test_depth_sort_wide_range(n, F, near, far):
     if n < 10000:
         pairs = obin.sorted_pairs(g, frames, cfg)
         assert np.array_equal(lists["pair_item"], (pairs["frame"] * n + pairs["index"]).astype(np.uint32))
+
+
+# frames sorted by one workgroup in LDS: every number of keys per thread it
+# has, at its limits, up to the largest frame and one past it; runs of equal
+# depths and culled items among them
+@pytest.mark.parametrize("n,F", [(63, 1), (1025, 3), (2048, 2), (2049, 1), (4096, 1), (4097, 2), (8192, 1), (8193, 2),
+                                 (16385, 2)])
+def test_depth_sort_small_frames(n, F):
+    W, H = 96, 72
+    g = scenes.draw_gaussians(n, W, H, 80.0, 80.0, seed=51)
+    rng = np.random.default_rng(52)
+    tie = rng.random(n) < 0.4
+    g.mean[2] = np.where(tie, np.float32([1.5, 2.5, 4.0])[rng.integers(0, 3, n)], g.mean[2])
+    g.mean[2, ::11] = np.float32(-1.0)
+    frames = scenes.identity_frames([0.1 * f for f in range(F)], W, H, 80.0, 80.0, 4)
+    cfg = scenes.RenderConfig(width=W, height=H)
+    res = run_gpu(g, frames, cfg, channels=("rgb",))
+    lists = gpu_lists(res, g, frames, cfg)
+    key = np.concatenate([obin.project(g, fr, cfg, f)["key"] for f, fr in enumerate(frames)]).astype(np.int64)
+    want = np.concatenate([f * n + np.argsort(key[f * n:(f + 1) * n], kind="stable") for f in range(F)])
+    np.testing.assert_array_equal(lists["depth_item"].astype(np.int64), want)
+    np.testing.assert_array_equal(lists["depth_key"].astype(np.int64), key[want])
+    rect = np.concatenate([obin.project(g, fr, cfg, f)["rect"].T for f, fr in enumerate(frames)])
+    valid = lists["count"] > 0
+    got = lists["rect"]
+    got = np.stack([got[:, 0] & 0xFFFF, got[:, 0] >> 16, got[:, 1] & 0xFFFF, got[:, 1] >> 16], 1)
+    np.testing.assert_array_equal(got[valid], rect[valid])
