@@ -529,12 +529,19 @@ __global__ void __launch_bounds__(1024) k_tile_keyscan(const uint32_t* __restric
     }
 }
 
-// Introspection: the sorted rectangles back in item order.
-__global__ void k_item_rects(const uint32_t* __restrict__ dval, const uint2* __restrict__ drect, long long M,
-                             uint2* __restrict__ out) {
+// Introspection: the sorted rectangles, and the tiles they cover, back in item
+// order.
+__global__ void k_item_rects(const uint32_t* __restrict__ dkey, const uint32_t* __restrict__ dval,
+                             const uint2* __restrict__ drect, long long M, uint2* __restrict__ rects,
+                             uint32_t* __restrict__ counts) {
     for (long long j = (long long)blockIdx.x * blockDim.x + threadIdx.x; j < M;
-         j += (long long)gridDim.x * blockDim.x)
-        out[dval[j]] = drect[j];
+         j += (long long)gridDim.x * blockDim.x) {
+        const uint2 r = drect[j];
+        if (rects) rects[dval[j]] = r;
+        uint32_t xlo, xhi, ylo, yhi;
+        unpack_rect(r, xlo, xhi, ylo, yhi);
+        if (counts) counts[dval[j]] = dkey[j] == kCulledKey ? 0u : (xhi - xlo + 1) * (yhi - ylo + 1);
+    }
 }
 
 // Introspection: expands the ranges into per-pair (frame, tile) keys.
@@ -636,11 +643,11 @@ hipError_t launch_binning(const Params& P, const Workspace& w, hipStream_t s) {
     return hipGetLastError();
 }
 
-void launch_item_rects(const Workspace& w, uint2* out, hipStream_t s) {
+void launch_item_rects(const Workspace& w, uint2* rects, uint32_t* counts, hipStream_t s) {
     if (w.M == 0) return;
     const long long blocks = (w.M + 255) / 256;
     hipLaunchKernelGGL(k_item_rects, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0, s,
-                       w.dval[1], w.drect[1], (long long)w.M, out);
+                       w.dkey[1], w.dval[1], w.drect[1], (long long)w.M, rects, counts);
 }
 
 void launch_tile_lists(const Params& P, const Workspace& w, hipStream_t s) {

@@ -317,7 +317,7 @@ int gftorf_copy_lists(const void* ws, int64_t n, int32_t n_frames, const gftorf_
     if (e != hipSuccess) return hip_fail(e, "gftorf_copy_lists");
     unsigned long long np = st.n_pairs < P.cap ? st.n_pairs : P.cap;
     if (pair_capacity >= 0 && np > (unsigned long long)pair_capacity) np = (unsigned long long)pair_capacity;
-    if (depth_key || depth_item || item_rect) gft::launch_sort_settle(w, s);
+    if (depth_key || depth_item || item_rect || item_count) gft::launch_sort_settle(w, s);
     auto cp = [&](void* dst, const void* src, size_t bytes) {
         if (dst && bytes && e == hipSuccess) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, s);
     };
@@ -332,9 +332,8 @@ int gftorf_copy_lists(const void* ws, int64_t n, int32_t n_frames, const gftorf_
     cp(pair_item, w.tval, 4 * np);
     cp(depth_key, w.dkey[1], 4 * (size_t)w.M);
     cp(depth_item, w.dval[1], 4 * (size_t)w.M);
-    cp(item_count, w.cnt, 4 * (size_t)w.M);
-    if (item_rect && e == hipSuccess) {
-        gft::launch_item_rects(w, reinterpret_cast<uint2*>(item_rect), s);
+    if ((item_rect || item_count) && e == hipSuccess) {
+        gft::launch_item_rects(w, reinterpret_cast<uint2*>(item_rect), item_count, s);
         e = hipGetLastError();
     }
     cp(tile_ranges, w.ranges, 8 * (size_t)P.F * P.n_tiles);

@@ -134,7 +134,6 @@ struct Workspace {
     Status* status;
     float4* rec;            // [M][record_float4s]
     float4* conic;          // [M]
-    uint32_t* cnt;          // [M] tiles covered
     uint8_t* touch;         // [M] 1 if the forward walked the item in some tile: only those have gradients
     uint32_t* nf_block;     // [ceil(n / 256)] non-finite Gaussians per preprocess block
     uint32_t* dkey[2];      // [M] depth keys (double buffer)
@@ -185,7 +184,6 @@ inline Workspace carve(void* base, int64_t n, int32_t F, int nf, int ntx, int nt
     w.status = reinterpret_cast<Status*>(take(sizeof(Status)));
     w.rec = reinterpret_cast<float4*>(take(sizeof(float4) * record_float4s(nf) * M));
     w.conic = reinterpret_cast<float4*>(take(sizeof(float4) * M));
-    w.cnt = reinterpret_cast<uint32_t*>(take(4 * M));
     w.touch = reinterpret_cast<uint8_t*>(take(M));
     w.nf_block = reinterpret_cast<uint32_t*>(take(4 * (size_t)((n + 255) / 256 + 1)));
     for (int i = 0; i < 2; ++i) w.dkey[i] = reinterpret_cast<uint32_t*>(take(4 * M));
@@ -250,7 +248,8 @@ void launch_sort_settle(const Workspace& w, hipStream_t s);   // sorted items to
 // sort's digit counts, not its control words alone.
 inline bool one_sweep_sort(const Params&, const Workspace& w) { return w.M > 0 && w.one_sweep; }
 hipError_t launch_binning(const Params& P, const Workspace& w, hipStream_t s);
-void launch_item_rects(const Workspace& w, uint2* out, hipStream_t s);
+// Rectangles and tile counts in item order, from buffer 1; either may be NULL.
+void launch_item_rects(const Workspace& w, uint2* rects, uint32_t* counts, hipStream_t s);
 void launch_tile_lists(const Params& P, const Workspace& w, hipStream_t s);   // completes every tile list
 void launch_keys_from_ranges(const Params& P, const Workspace& w, uint32_t* keys,
                              unsigned long long limit, hipStream_t s);

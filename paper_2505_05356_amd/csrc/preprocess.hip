@@ -10,8 +10,11 @@
 // (rectangle, key) is evaluated in binary64 in one fixed operation order with
 // FMA contraction off, so the lists are reproducible bit for bit.
 //
-// Layout: one thread per Gaussian; the thread loops over the frames so the
-// 24 parameter floats of a Gaussian are read from HBM once per batch.
+// Layout: one thread per Gaussian; the thread loops over the frames (over some
+// of them where the Gaussians are few) so the 24 parameter floats of a
+// Gaussian are read from HBM once per batch.  Bound by its binary64
+// arithmetic, some 800 vector instructions an item (1M x 16 frames: 370 us,
+// of which the 1.2 GB that it writes take 210).
 // Outputs are indexed by item i = frame * n + gaussian, so consecutive
 // threads write consecutive records.
 #include "common.h"
@@ -66,7 +69,7 @@ struct Binned {
 // The pinned binary64 operation sequence.  Every statement is one IEEE
 // operation evaluated left to right; contraction is off in this scope.
 __device__ Binned bin(const Gauss& G, const gftorf_frame& fr, const Params& P,
-                      const double* dl) {
+                      bool has_dl, const double (&dl)[3]) {
 #pragma clang fp contract(off)
     Binned b;
     const double t = (double)fr.time;
@@ -85,7 +88,7 @@ __device__ Binned bin(const Gauss& G, const gftorf_frame& fr, const Params& P,
     } else {
         for (int c = 0; c < 3; ++c) b.m[c] = (G.x0[c] + G.v[c] * t) + (0.5 * G.a[c]) * tt;
     }
-    if (dl)   // the deformation network's offset of this frame (§4), added last
+    if (has_dl)   // the deformation network's offset of this frame (§4), added last
         for (int c = 0; c < 3; ++c) b.m[c] = b.m[c] + dl[c];
 
     const double w0 = G.q0[0], qx0 = G.q0[1], qy0 = G.q0[2], qz0 = G.q0[3];
@@ -181,31 +184,43 @@ template <bool SH>
 __global__ void __launch_bounds__(256) k_preprocess(Params P, gftorf_gaussians g,
                                                     const gftorf_frame* __restrict__ frames,
                                                     float4* __restrict__ rec, float4* __restrict__ conic,
-                                                    uint2* __restrict__ rect,
-                                                    uint32_t* __restrict__ cnt, uint32_t* __restrict__ dkey,
+                                                    uint2* __restrict__ rect, uint32_t* __restrict__ dkey,
                                                     uint32_t* __restrict__ nf_block,
-                                                    uint32_t* __restrict__ sclear, int64_t nclear) {
+                                                    uint32_t* __restrict__ sclear, int64_t nclear, int per) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int f0 = (int)blockIdx.y * per, f1 = min(f0 + per, (int)P.F);
     const Gauss G = load_gauss(g, k < P.n ? k : 0);
     // non-finite Gaussians per block (summed by the tile-range scan)
     const int bad = __syncthreads_count(k < P.n && !G.finite);
-    if (threadIdx.x == 0) nf_block[blockIdx.x] = (uint32_t)bad;
+    if (threadIdx.x == 0 && f0 == 0) nf_block[blockIdx.x] = (uint32_t)bad;
     // the depth sort's control words and digit counts start at 0
-    for (int64_t i = k; i < nclear; i += (int64_t)gridDim.x * blockDim.x)
+    for (int64_t i = (int64_t)blockIdx.y * gridDim.x * blockDim.x + k; i < nclear;
+         i += (int64_t)gridDim.y * gridDim.x * blockDim.x)
         sclear[i] = 0u;
     if (k >= P.n) return;
+    // the harmonics' coefficients of this thread's Gaussian, read once for all
+    // its frames; LDS because the registers are taken (two workgroups share a
+    // CU either way).  100k Gaussians x 4 and x 16 frames: 23 and 55 us; 33 and
+    // 95 us with the coefficients read again for every frame.
+    __shared__ float coef[SH ? 4 * kMaxSH : 1][SH ? 256 : 1];
+    const int K = SH ? sh_count(g.sh_degree) : 0;
+    if constexpr (SH) {
+        if (g.sh_rgb)
+#pragma unroll 16
+            for (int i = 0; i < 3 * K; ++i) coef[i][threadIdx.x] = g.sh_rgb[(int64_t)i * P.n + k];
+        if (g.sh_albedo)
+#pragma unroll 16
+            for (int l = 0; l < K; ++l) coef[3 * kMaxSH + l][threadIdx.x] = g.sh_albedo[(int64_t)l * P.n + k];
+    }
     const int RS4 = record_float4s(P.nf);
     const double o = 1.0 / (1.0 + exp(-G.logit));
-    for (int f = 0; f < P.F; ++f) {
+    for (int f = f0; f < f1; ++f) {
         const gftorf_frame& fr = frames[f];
-        double dl[3];
+        double dl[3] = {0.0, 0.0, 0.0};
         if (g.delta)
             for (int c = 0; c < 3; ++c) dl[c] = (double)g.delta[((int64_t)f * 3 + c) * P.n + k];
-        const Binned b = bin(G, fr, P, g.delta ? dl : nullptr);
+        const Binned b = bin(G, fr, P, g.delta != nullptr, dl);
         const int64_t item = (int64_t)f * P.n + k;
-        uint32_t c = 0;
-        if (b.valid) c = (uint32_t)((b.xhi - b.xlo + 1) * (b.yhi - b.ylo + 1));
-        cnt[item] = c;
         rect[item] = make_uint2((uint32_t)b.xlo | ((uint32_t)(b.xhi & 0xffff) << 16),
                                 (uint32_t)b.ylo | ((uint32_t)(b.yhi & 0xffff) << 16));
         dkey[item] = b.valid ? __float_as_uint((float)b.p[2]) : kCulledKey;
@@ -230,21 +245,18 @@ __global__ void __launch_bounds__(256) k_preprocess(Params P, gftorf_gaussians g
             const float id = (float)(1.0 / d);
             float Y[kMaxSH];
             sh_basis((float)e0 * id, (float)e1 * id, (float)e2 * id, g.sh_degree, Y);
-            const int K = sh_count(g.sh_degree);
-            const int64_t n = P.n;
-            // degree 3 (all kMaxSH coefficients present): unguarded loads, so
-            // they issue together instead of one guarded load at a time
+            // degree 3 (all kMaxSH coefficients present): unguarded reads
             const bool full = K == kMaxSH;
             if (g.sh_rgb)
                 for (int c = 0; c < 3; ++c) {
                     float acc = 0.5f;
                     if (full) {
 #pragma unroll
-                        for (int l = 0; l < kMaxSH; ++l) acc += Y[l] * g.sh_rgb[((int64_t)l * 3 + c) * n + k];
+                        for (int l = 0; l < kMaxSH; ++l) acc += Y[l] * coef[3 * l + c][threadIdx.x];
                     } else {
 #pragma unroll
                         for (int l = 0; l < kMaxSH; ++l)
-                            if (l < K) acc += Y[l] * g.sh_rgb[((int64_t)l * 3 + c) * n + k];
+                            if (l < K) acc += Y[l] * coef[3 * l + c][threadIdx.x];
                     }
                     rgb[c] = fmaxf(acc, 0.0f);
                 }
@@ -252,19 +264,23 @@ __global__ void __launch_bounds__(256) k_preprocess(Params P, gftorf_gaussians g
                 float acc = 0.5f;
                 if (full) {
 #pragma unroll
-                    for (int l = 0; l < kMaxSH; ++l) acc += Y[l] * g.sh_albedo[(int64_t)l * n + k];
+                    for (int l = 0; l < kMaxSH; ++l) acc += Y[l] * coef[3 * kMaxSH + l][threadIdx.x];
                 } else {
 #pragma unroll
                     for (int l = 0; l < kMaxSH; ++l)
-                        if (l < K) acc += Y[l] * g.sh_albedo[(int64_t)l * n + k];
+                        if (l < K) acc += Y[l] * coef[3 * kMaxSH + l][threadIdx.x];
                 }
                 albedo = (double)fmaxf(acc, 0.0f);
             }
         }
         r[1] = make_float4(rgb[0], rgb[1], rgb[2], (float)d);
         const double amp = (double)P.s_int * albedo / (d * d);
-        float ph[2 * GFTORF_MAX_FREQ];
-        for (int fi = 0; fi < P.nf; ++fi) {
+        float ph[2 * GFTORF_MAX_FREQ];   // indexed by constants only: in registers
+#pragma unroll
+        for (int fi = 0; fi < GFTORF_MAX_FREQ; ++fi) {
+            ph[2 * fi] = 0.f;
+            ph[2 * fi + 1] = 0.f;
+            if (fi >= P.nf) continue;
             // psi = 4 pi f d / c = 2 pi * cycles; the fractional cycle is taken in
             // binary64 (psi reaches tens of radians), then one float32 sine and
             // cosine of 2 pi * frac (the hardware instructions take revolutions)
@@ -275,12 +291,9 @@ __global__ void __launch_bounds__(256) k_preprocess(Params P, gftorf_gaussians g
             ph[2 * fi] = (float)amp * sn;
             ph[2 * fi + 1] = (float)amp * cs;
         }
-        for (int fi = P.nf; fi < 2 * ((P.nf + 1) / 2); ++fi) {
-            ph[2 * fi] = 0.f;
-            ph[2 * fi + 1] = 0.f;
-        }
-        for (int j = 0; j < (P.nf + 1) / 2; ++j)
-            r[2 + j] = make_float4(ph[4 * j], ph[4 * j + 1], ph[4 * j + 2], ph[4 * j + 3]);
+#pragma unroll
+        for (int j = 0; j < (GFTORF_MAX_FREQ + 1) / 2; ++j)
+            if (j < (P.nf + 1) / 2) r[2 + j] = make_float4(ph[4 * j], ph[4 * j + 1], ph[4 * j + 2], ph[4 * j + 3]);
     }
 }
 
@@ -299,7 +312,7 @@ __global__ void __launch_bounds__(256) k_preprocess(Params P, gftorf_gaussians g
 // forward walked and gives its lanes to them alone: the list of an opaque tile
 // ends early, so of 1M Gaussians x 16 frames 4% have a gradient, of 200k x 8
 // 10%.  Before, every item's record was read and its whole chain evaluated
-// for zeros: 653 -> 71 us and 69 -> 21 us.
+// for zeros: 653 -> 70 us and 69 -> 19 us.
 // ---------------------------------------------------------------------------
 template <int CTRL>
 __device__ __forceinline__ float dpp_f(float x) {
@@ -742,6 +755,8 @@ __global__ void __launch_bounds__(256) k_preprocess_bwd(Params P, gftorf_gaussia
 
 }  // namespace
 
+constexpr unsigned kPreprocessGroups = 512;
+
 void launch_preprocess(const Params& P, const gftorf_gaussians& g, const gftorf_frame* frames,
                        const Workspace& w, hipStream_t s) {
     const int threads = 256;
@@ -749,13 +764,22 @@ void launch_preprocess(const Params& P, const gftorf_gaussians& g, const gftorf_
     if (blocks == 0) return;
     const int64_t nclear =
         kSortCtlWords + (one_sweep_sort(P, w) ? (int64_t)P.F * (kSortPasses + 1) * kSortBuckets : 0);
+    // frames per thread: all of them, unless that leaves the chip's 512
+    // resident workgroups idle; then the frames are split over grid y, each
+    // part reading the Gaussians again (4000 Gaussians x 12 frames: 26 us
+    // unsplit, 8 split; 30k x 8: 23 and 14)
+    int parts = (int)(kPreprocessGroups / blocks);
+    if (parts > P.F) parts = P.F;
+    if (parts < 1) parts = 1;
+    const int per = (P.F + parts - 1) / parts;
+    const dim3 grid(blocks, (unsigned)((P.F + per - 1) / per));
     { ProfScope _p("k_preprocess", s);
     if (g.sh_rgb || g.sh_albedo)
-        hipLaunchKernelGGL(k_preprocess<true>, dim3(blocks), dim3(threads), 0, s, P, g, frames, w.rec,
-                           w.conic, w.drect[0], w.cnt, w.dkey[0], w.nf_block, w.sctl, nclear);
+        hipLaunchKernelGGL(k_preprocess<true>, grid, dim3(threads), 0, s, P, g, frames, w.rec,
+                           w.conic, w.drect[0], w.dkey[0], w.nf_block, w.sctl, nclear, per);
     else
-        hipLaunchKernelGGL(k_preprocess<false>, dim3(blocks), dim3(threads), 0, s, P, g, frames, w.rec,
-                           w.conic, w.drect[0], w.cnt, w.dkey[0], w.nf_block, w.sctl, nclear);
+        hipLaunchKernelGGL(k_preprocess<false>, grid, dim3(threads), 0, s, P, g, frames, w.rec,
+                           w.conic, w.drect[0], w.dkey[0], w.nf_block, w.sctl, nclear, per);
     }
 }
 
@@ -777,10 +801,12 @@ void launch_preprocess_bwd(const Params& P, const gftorf_gaussians& g, const gft
     int gs = 1;
     while (gs < P.F && gs < 64) gs *= 2;
     const int threads = 256;
-    // Gaussians per workgroup: as many as leave about 1024 workgroups, at
-    // least one round of the lanes and at most one per thread
+    // Gaussians per workgroup: as many as leave about 256 workgroups, at least
+    // one round of the lanes and at most one per thread (100k Gaussians of
+    // degree-3 harmonics x 4 and x 16 frames, against 1024 workgroups: 24 and
+    // 52 us, 34 and 64 us)
     int ng = threads;
-    while (ng > threads / gs && P.n < (int64_t)ng * 1024) ng /= 2;
+    while (ng > threads / gs && P.n < (int64_t)ng * 256) ng /= 2;
     const unsigned blocks = (unsigned)((P.n + ng - 1) / ng);
     if (blocks == 0) return;
     ProfScope _p("k_preprocess_bwd", s);

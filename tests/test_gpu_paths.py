@@ -73,7 +73,7 @@ def test_large_batch_split_equals_small(tile, n_freq):
 
 
 # the preprocess backward packs the walked Gaussians of a workgroup when it
-# has more than one round of them (here 64 Gaussians, 16 or 8 a round), and
+# has more than one round of them (here 256 Gaussians, 16 or 8 a round), and
 # writes zeros for the others: against the per-frame calls, which do not pack
 @pytest.mark.parametrize("n_frames,sh", [(9, False), (17, False), (9, True)])
 def test_packed_preprocess_backward(n_frames, sh):
@@ -173,3 +173,31 @@ def test_depth_sort_small_frames(n, F):
     got = lists["rect"]
     got = np.stack([got[:, 0] & 0xFFFF, got[:, 0] >> 16, got[:, 1] & 0xFFFF, got[:, 1] >> 16], 1)
     np.testing.assert_array_equal(got[valid], rect[valid])
+
+
+# the preprocess splits the frames of few Gaussians over workgroups: every
+# frame in its own, several frames in each of some, all in one; with the
+# harmonics' coefficients of every degree kept for all of a thread's frames
+@pytest.mark.parametrize("n,F,degree", [(300, 7, 0), (300, 7, None), (40_000, 5, None), (40_000, 5, 1), (40_000, 5, 3),
+                                        (131_073, 3, 2)])
+def test_preprocess_frame_split(n, F, degree):
+    g = scenes.draw_gaussians(n, 64, 48, 60.0, 60.0, seed=4, dynamic=True, log_scale_mean=float(np.log(0.02)))
+    if degree is not None:
+        g = scenes.with_sh(g, degree=degree, seed=1)
+    g.mean[0, 5] = np.nan   # counted once however the frames are split
+    cfg = scenes.RenderConfig(width=64, height=48, freqs=(30e6, 60e6, 20e6))
+    frames = scenes.identity_frames(np.linspace(0.0, 0.3, F), 64, 48, 60.0, 60.0, cfg.n_quad, n_freq=3)
+    res = run_gpu(g, frames, cfg)
+    lists = gpu_lists(res, g, frames, cfg)
+    assert res["status"]["nonfinite"] == 1
+    for f in range(F):
+        one = run_gpu(g, frames[f:f + 1], cfg)
+        l1 = gpu_lists(one, g, frames[f:f + 1], cfg)
+        sel = slice(f * n, (f + 1) * n)
+        np.testing.assert_array_equal(lists["depth_key"][sel], l1["depth_key"])
+        np.testing.assert_array_equal(lists["depth_item"][sel] - np.uint32(f * n), l1["depth_item"])
+        np.testing.assert_array_equal(lists["count"][sel], l1["count"])
+        np.testing.assert_array_equal(lists["rect"][sel], l1["rect"])
+        ok = np.ones((1, 48, 64), bool)
+        for k in ("rgb", "quad", "depth"):
+            assert_images_close(res[k][f:f + 1], one[k], ok, k, rtol=1e-6)
