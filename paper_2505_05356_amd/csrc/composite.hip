@@ -79,6 +79,30 @@ __device__ __forceinline__ float4 stage_centre(const float4 r0, float o, float o
     return make_float4(cu, cv, (lamin - __log2f(o)) - kSkipMargin, last);
 }
 
+// Pixel centres [x0, x1] x [y0, y1] relative to the tile origin.
+struct PixelBox {
+    float x0, x1, y0, y1;
+};
+
+// True only if no pixel of the box can take the entry: alpha < alpha_min at
+// all of them, whatever the rounding.  The exponent's maximum over the box is
+// 0 at the centre if the box holds it, else on an edge that faces the centre;
+// err covers the rounding of this bound and of the pixels' own exponents.
+// Anything that is not a number compares false, and the entry is kept.
+__device__ __forceinline__ bool never_taken(const float4 c, const float4 r1, float lamin, const PixelBox& b) {
+    const float dx0 = b.x0 - c.x, dx1 = b.x1 - c.x, dy0 = b.y0 - c.y, dy1 = b.y1 - c.y;
+    const float ex = fminf(fmaxf(0.f, dx0), dx1), ey = fminf(fmaxf(0.f, dy0), dy1);
+    const float hb = -0.5f * r1.y;
+    const float ys = fminf(fmaxf(hb * ex * __builtin_amdgcn_rcpf(r1.z), dy0), dy1);
+    const float xs = fminf(fmaxf(hb * ey * __builtin_amdgcn_rcpf(r1.x), dx0), dx1);
+    const float qx = ys * (r1.z * ys + r1.y * ex) + r1.x * ex * ex;
+    const float qy = ey * (r1.z * ey + r1.y * xs) + r1.x * xs * xs;
+    const float mx = fmaxf(fabsf(dx0), fabsf(dx1)), my = fmaxf(fabsf(dy0), fabsf(dy1));
+    const float err = 2e-6f * (fabsf(r1.x) * mx * mx + fabsf(r1.y) * mx * my + fabsf(r1.z) * my * my);
+    const float thr = (lamin - __log2f(r1.w)) - kSkipMargin;
+    return fmaxf(qx, qy) + err < thr && qx == qx && qy == qy;
+}
+
 // Sum over the 64 lanes of a wave: DPP within rows of 16, then 4 readlanes.
 template <int CTRL>
 __device__ __forceinline__ float dpp_f32(float x) {
@@ -227,11 +251,15 @@ __device__ __forceinline__ void write_pixel(const Params& P, const gftorf_frame&
 // Bound by vector instruction issue in large batches and by the length of one
 // wave's instruction stream in small ones, so everything that is the same for
 // a whole wave (who takes the entry, who stops, the workload counts) is kept
-// as lane masks in scalar registers: 1M Gaussians x 16 frames 803 -> 648 us,
-// 200k x 8 172 -> 142 us, one 640x480 frame of 100k 41 -> 36 us, 12 tiles of
-// 2k Gaussians 51 -> 44 us against one pixel per lane in divergent branches.
+// as lane masks in scalar registers, and a wave only walks the entries that
+// some pixel of its box may take: of those that its tile's list holds, 46% in
+// an image of 64 x 48 pixels and 80% in the batches below.  One lane tests
+// one entry while it is staged.  1M Gaussians x 16 frames 803 us with one
+// pixel per lane in divergent branches, 645 with lane masks, 611 now; 200k x 8
+// 172, 155, 142; one 640x480 frame of 100k 41, 38, 36; 12 tiles of 2k
+// Gaussians 51, 48, 33.
 template <int TW, int TH, int NF, int WPT, int U>
-__global__ void __launch_bounds__(64 * WPT) k_composite_fwd(Params P, const gftorf_frame* __restrict__ frames,
+__global__ void __launch_bounds__(64 * WPT, WPT == 2 && NF <= 2 ? 6 : 1) k_composite_fwd(Params P, const gftorf_frame* __restrict__ frames,
                                                             const uint2* __restrict__ ranges,
                                                             const uint2* __restrict__ granges,
                                                             const uint32_t* __restrict__ gval,
@@ -247,15 +275,17 @@ __global__ void __launch_bounds__(64 * WPT) k_composite_fwd(Params P, const gfto
     constexpr int RS4 = record_float4s(NF);
     constexpr int SS4 = staged_float4s(NF);
     // 64 list entries are staged at a time (most pixels stop after 100-200, so
-    // short batches waste few loads).  SHARED: the workgroup's waves find and
-    // stage them together; otherwise each for itself, in its own slice.
+    // short batches waste few loads), by each wave for itself: those that some
+    // pixel of its box may take, one after the other, then U that none takes.
+    // SHARED: the workgroup's waves find the entries together.
     constexpr bool SHARED = WPT == 4;
     constexpr int NQ = SHARED ? 1 : WPT;
-    __shared__ float4 srec_w[NQ][SS4][64];
+    __shared__ float4 srec_w[WPT][SS4][64 + U];
     // group-list entries of the tile found but not yet staged: fewer than a
     // batch, and one round of the walk more
     constexpr uint32_t QN = SHARED ? 2048 : 512;
     __shared__ uint32_t queue_w[NQ][QN];
+    __shared__ uint32_t place_w[WPT][64];   // of a staged entry in its batch
     __shared__ uint32_t found_w[2][WPT], going_w[2][WPT];   // SHARED: per wave, by turn
 
     const int w = xcd_remap(blockIdx.x, gridDim.x);
@@ -268,22 +298,29 @@ __global__ void __launch_bounds__(64 * WPT) k_composite_fwd(Params P, const gfto
     const uint2 rg = ranges[w];
     const float amin = P.alpha_min, amax = P.alpha_max, tmin = P.T_min;
 
+    // A wave's pixels form a box of BW x BH, as square as one column per lane
+    // lets it be, so that many of its tile's entries miss it.
+    constexpr int BW = TW == 32 && PPT > 1 ? 16 : 8, BH = 64 / BW * PPT, STEP = 64 / BW;
+    static_assert(TW % BW == 0 && TH % BH == 0, "whole boxes");
+    const int bx = sub % (TW / BW) * BW, by = sub / (TW / BW) * BH;
+    const int px = bx + lane % BW, py = by + lane / BW;   // its pixels: (px, py + STEP i)
+    const float lamin = amin > 0.f ? __log2f(amin) : -INFINITY;
+    const PixelBox box = {(float)bx + 0.5f, (float)(bx + BW) - 0.5f, (float)by + 0.5f, (float)(by + BH) - 0.5f};
     // pixel centre relative to the tile origin (exact small values); a pixel
     // that has stopped (or lies outside) has an unreachable threshold
-    const int p0 = lane + 64 * sub;
-    const float fpx = (float)(p0 % TW) + 0.5f;
+    const float fpx = (float)px + 0.5f;
     float fpy[PPT], T[PPT], cr[PPT], cg[PPT], cb[PPT], dep[PPT], S[PPT][NF], C[PPT][NF], thr[PPT];
     uint32_t last[PPT];
     uint64_t alive[PPT], any = 0ull;
 #pragma unroll
     for (int i = 0; i < PPT; ++i) {
-        const int row = p0 / TW + i * (64 * WPT / TW);
+        const int row = py + STEP * i;
         fpy[i] = (float)row + 0.5f;
         T[i] = 1.0f;
         cr[i] = cg[i] = cb[i] = dep[i] = 0.f;
 #pragma unroll
         for (int k = 0; k < NF; ++k) S[i][k] = C[i][k] = 0.f;
-        const bool inside = tx * TW + p0 % TW < P.W && ty * TH + row < P.H;
+        const bool inside = tx * TW + px < P.W && ty * TH + row < P.H;
         thr[i] = inside ? amin : INFINITY;
         last[i] = 0;
         alive[i] = lanes(inside);
@@ -293,7 +330,8 @@ __global__ void __launch_bounds__(64 * WPT) k_composite_fwd(Params P, const gfto
     // stops at entry e has evaluated e of them, one that never stops all
     uint32_t n_eval = 0, n_comp = 0;
 
-    float4 (*srec)[64] = srec_w[SHARED ? 0 : sub];
+    float4 (*srec)[64 + U] = srec_w[sub];
+    uint32_t* place = place_w[sub];
     uint32_t* queue = queue_w[SHARED ? 0 : sub];
     auto sync = [] {   // LDS writes before this, reads after it, and the other way round
         if constexpr (SHARED) {
@@ -341,43 +379,55 @@ __global__ void __launch_bounds__(64 * WPT) k_composite_fwd(Params P, const gfto
         cnt = __builtin_amdgcn_readfirstlane((int)min(min(queued, 64u), len - pos));
         if (cnt == 0) break;   // the list is cut at the pair capacity
         if (pos != 0u && pos / 64u <= n_marks) {   // for the split backward; pos is a multiple of 64
-            float* m = marks + ((size_t)w * n_marks + (pos / 64u - 1u)) * (TW * TH) + p0;
+            float* m = marks + ((size_t)w * n_marks + (pos / 64u - 1u)) * (TW * TH) + py * TW + px;
 #pragma unroll
-            for (int i = 0; i < PPT; ++i) m[64 * WPT * i] = T[i];
+            for (int i = 0; i < PPT; ++i) m[STEP * TW * i] = T[i];
         }
-        sync();
-        {   // stage; past the end: alpha = -1, below every threshold
-            const bool have = lane < cnt;
-            if (have && (!SHARED || sub == 0))
-                tval[rg.x + pos + lane] = item;   // the backward walks the part that was composited
-            const float4* r = rec + (size_t)item * RS4;
+        const bool have = lane < cnt;
+        if (have && (!SHARED || sub == 0))
+            tval[rg.x + pos + lane] = item;   // the backward walks the part that was composited
+        const float4* r = rec + (size_t)item * RS4;
+        float4 c = make_float4(0.f, 0.f, 0.f, 0.f), r1 = make_float4(0.f, 0.f, 0.f, -1.f);
+        if (have) {
+            c = r[0];
+            r1 = conic[item];
+        }
+        c = make_float4((c.x - ox) + c.z, (c.y - oy) + c.w, 0.f, 0.f);
+        const uint64_t hits = lanes(have) & ~lanes(never_taken(c, r1, lamin, box));
+        const uint32_t slot = rank_below(hits), n_hits = (uint32_t)__popcll(hits);
+        float4 fields[SS4 - 2];
 #pragma unroll
-            for (int q = 0; q < SS4; ++q) {   // SHARED: a slot per wave
-                if (SHARED && q % WPT != sub) continue;
-                if (q == 0) {
-                    float4 c = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (have) {
-                        const float4 r0 = r[0];
-                        c = make_float4((r0.x - ox) + r0.z, (r0.y - oy) + r0.w, 0.f, 0.f);
-                    }
-                    srec[0][lane] = c;
-                } else if (q == 1) {
-                    srec[1][lane] = have ? conic[item] : make_float4(0.f, 0.f, 0.f, -1.f);
-                } else if (have) {
-                    srec[q][lane] = r[q - 1];
-                }
-            }
+        for (int q = 2; q < SS4; ++q) fields[q - 2] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (lane_of(hits))
+#pragma unroll
+            for (int q = 2; q < SS4; ++q) fields[q - 2] = r[q - 1];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // after the last batch's reads
+        __builtin_amdgcn_wave_barrier();
+        if (lane < U) {   // alpha = -1, below every threshold
+            srec[0][n_hits + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
+            srec[1][n_hits + lane] = make_float4(0.f, 0.f, 0.f, -1.f);
         }
-        sync();
+        if (lane_of(hits)) {
+            srec[0][slot] = c;
+            srec[1][slot] = r1;
+            place[slot] = (uint32_t)lane;
+        }
+        if constexpr (SHARED) __syncthreads();   // every wave has its items: the queue may be written
         head = (head + (uint32_t)cnt) % QN;
         queued -= (uint32_t)cnt;
         // the next batch's entries are found, and their items loaded, while
-        // this one is walked
+        // the rest of this one arrives and while it is walked
         const uint32_t walked = item;
         next_items();
+        if (lane_of(hits))
+#pragma unroll
+            for (int q = 2; q < SS4; ++q) srec[q][slot] = fields[q - 2];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
         const uint32_t pos0 = pos + 1u;   // list position of the batch's first entry
-        int k0 = 0;
-        for (; k0 < cnt && any != 0ull; k0 += U) {
+        constexpr uint32_t kStaged = 0x80000000u;   // `last` holds a staged entry's index
+        uint32_t k0 = 0;
+        for (; k0 < n_hits && any != 0ull; k0 += U) {
             float a[U][PPT];
             float4 fld[U][SS4 - 2];
 #pragma unroll
@@ -409,7 +459,7 @@ __global__ void __launch_bounds__(64 * WPT) k_composite_fwd(Params P, const gfto
                         thr[i] = lane_of(stop) ? INFINITY : thr[i];
                         take &= ~stop;
                         alive[i] &= ~stop;
-                        n_eval += (uint32_t)__popcll(stop) * (pos0 + (uint32_t)(k0 + u));
+                        n_eval += (uint32_t)__popcll(stop) * (pos0 + (uint32_t)__builtin_amdgcn_readfirstlane((int)place[k0 + u]));
                         any = 0ull;
 #pragma unroll
                         for (int q = 0; q < PPT; ++q) any |= alive[q];
@@ -429,12 +479,15 @@ __global__ void __launch_bounds__(64 * WPT) k_composite_fwd(Params P, const gfto
                             C[i][k] += ((k & 1) ? rp.w : rp.y) * w2;
                         }
                         T[i] = nT;
-                        last[i] = pos0 + (uint32_t)(k0 + u);
+                        last[i] = kStaged | (k0 + u);
                     }
                 }
         }
+#pragma unroll
+        for (int i = 0; i < PPT; ++i)
+            if (last[i] & kStaged) last[i] = pos0 + place[last[i] & 63u];
         // what no pixel walked has no gradient: the backward skips its record
-        if (lane < min(k0, cnt)) touch[walked] = 1;
+        if (lane_of(hits) && slot < k0) touch[walked] = 1;
         going = any != 0ull;
         if constexpr (SHARED) {
             const int t = (int)(pos / 64u) & 1;
@@ -470,7 +523,7 @@ __global__ void __launch_bounds__(64 * WPT) k_composite_fwd(Params P, const gfto
     const gftorf_frame& fr = frames[f];
     const size_t HW = (size_t)P.H * P.W;
     for (int i = 0; i < PPT; ++i) {
-        const int x = tx * TW + p0 % TW, y = ty * TH + p0 / TW + i * (64 * WPT / TW);
+        const int x = tx * TW + px, y = ty * TH + py + STEP * i;
         if (x < P.W && y < P.H)
             write_pixel<NF>(P, fr, out, f, HW, (size_t)y * P.W + x, cr[i], cg[i], cb[i], dep[i], S[i], C[i], T[i],
                             last[i]);

@@ -201,3 +201,29 @@ def test_preprocess_frame_split(n, F, degree):
         ok = np.ones((1, 48, 64), bool)
         for k in ("rgb", "quad", "depth"):
             assert_images_close(res[k][f:f + 1], one[k], ok, k, rtol=1e-6)
+
+
+# the forward's waves leave out the entries that no pixel of their box can
+# take: thin and round splats in every direction, opacities down to alpha_min
+# and below, nothing below any threshold (alpha_min 0), boxes cut by the image
+@pytest.mark.parametrize("tile,size", [((8, 8), (61, 45)), ((16, 16), (61, 45)), ((32, 8), (70, 45)),
+                                       ((16, 16), (1030, 1021)), ((32, 8), (1030, 1021))])
+@pytest.mark.parametrize("alpha_min", [1.0 / 255.0, 0.0, 0.05])
+def test_forward_box_test(tile, size, alpha_min):
+    W, H = size
+    n = 700
+    g = scenes.draw_gaussians(n, W, H, 1.2 * W, 1.2 * W, seed=W,
+                              log_scale_mean=float(np.log((2.0 if W < 100 else 12.0) / W)))
+    rng = np.random.default_rng(7)
+    g.scale[:] = (g.scale * np.exp(rng.uniform(-2.5, 2.5, g.scale.shape))).astype(np.float32)
+    g.quat[:] = rng.normal(size=g.quat.shape).astype(np.float32)
+    g.opacity_logit[:] = rng.uniform(-6.0, 3.0, n).astype(np.float32)
+    cfg = scenes.RenderConfig(width=W, height=H, tile_w=tile[0], tile_h=tile[1], alpha_min=alpha_min)
+    frames = scenes.identity_frames([0.0], W, H, 1.2 * W, 1.2 * W, cfg.n_quad, bg_seed=1)
+    ref = oref.render(g, frames, cfg)
+    ok = ~ref["flagged"]
+    assert ok.mean() > 0.9
+    res = run_gpu(g, frames, cfg)
+    for k in ("rgb", "quad", "depth", "T_final"):
+        assert_images_close(res[k], ref[k], ok, k)
+    np.testing.assert_array_equal(res["n_contrib"][ok], ref["n_contrib"][ok])
