@@ -529,6 +529,47 @@ __global__ void __launch_bounds__(1024) k_tile_keyscan(const uint32_t* __restric
     }
 }
 
+// The status header and the sums of the forward's per-work-item counts, to
+// host memory: one launch in place of a copy of the header, a second copy of
+// all counts and their sum on the host (a pass through autograd, with and
+// without: 2 frames of 97x75 pixels 293 and 263 us, one of 640x480 380 and
+// 350).
+__global__ void __launch_bounds__(1024) k_status_report(const Status* __restrict__ status, StatusReport* host) {
+    __shared__ unsigned long long part[2][16];
+    const Status st = *status;
+    unsigned long long ev = 0, co = 0;
+    if (st.magic == kStatusMagic && st.n_items <= (1ull << 26) && st.wcount_off >= sizeof(Status) &&
+        st.wcount_off % 8 == 0 && st.wcount_off < (1ull << 44)) {
+        const uint2* wcount = reinterpret_cast<const uint2*>(reinterpret_cast<const char*>(status) + st.wcount_off);
+        for (unsigned long long i = threadIdx.x; i < st.n_items; i += 8 * 1024) {
+            uint2 v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = i + 1024 * q < st.n_items ? wcount[i + 1024 * q] : make_uint2(0u, 0u);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                ev += v[q].x;
+                co += v[q].y;
+            }
+        }
+    }
+    ev = wave_reduce_sum(ev);
+    co = wave_reduce_sum(co);
+    if (threadIdx.x % 64 == 0) {
+        part[0][threadIdx.x / 64] = ev;
+        part[1][threadIdx.x / 64] = co;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 16; ++w) {
+            ev += part[0][w];
+            co += part[1][w];
+        }
+        host->st = st;
+        host->n_evaluated = ev;
+        host->n_composited = co;
+    }
+}
+
 // Introspection: the sorted rectangles, and the tiles they cover, back in item
 // order.
 __global__ void k_item_rects(const uint32_t* __restrict__ dkey, const uint32_t* __restrict__ dval,
@@ -648,6 +689,10 @@ void launch_item_rects(const Workspace& w, uint2* rects, uint32_t* counts, hipSt
     const long long blocks = (w.M + 255) / 256;
     hipLaunchKernelGGL(k_item_rects, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0, s,
                        w.dkey[1], w.dval[1], w.drect[1], (long long)w.M, rects, counts);
+}
+
+void launch_status_report(const void* ws, StatusReport* host, hipStream_t s) {
+    hipLaunchKernelGGL(k_status_report, dim3(1), dim3(1024), 0, s, static_cast<const Status*>(ws), host);
 }
 
 void launch_tile_lists(const Params& P, const Workspace& w, hipStream_t s) {

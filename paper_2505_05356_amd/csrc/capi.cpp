@@ -6,6 +6,7 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -256,13 +257,81 @@ int gftorf_render_bwd(const gftorf_gaussians* g, const gftorf_frame* frames, int
     return GFTORF_OK;
 }
 
+namespace {
+
+// Pinned host memory for one status report, out of a list that holds as many
+// as there were calls at once.
+struct PinnedReport {
+    gft::StatusReport report;
+    PinnedReport* next;
+};
+std::mutex g_reports_mutex;
+PinnedReport* g_reports = nullptr;
+
+PinnedReport* take_report() {
+    {
+        std::lock_guard<std::mutex> lock(g_reports_mutex);
+        if (PinnedReport* p = g_reports) {
+            g_reports = p->next;
+            return p;
+        }
+    }
+    void* p = nullptr;
+    return hipHostMalloc(&p, sizeof(PinnedReport), hipHostMallocPortable) == hipSuccess ? static_cast<PinnedReport*>(p)
+                                                                                       : nullptr;
+}
+
+void give_report(PinnedReport* p) {
+    std::lock_guard<std::mutex> lock(g_reports_mutex);
+    p->next = g_reports;
+    g_reports = p;
+}
+
+// The workspace lies in the memory of the current device, and the stream is
+// one of its streams: a kernel can read it there.
+bool on_current_device(const void* ws, hipStream_t s) {
+    int dev = -1;
+    hipDevice_t of_stream = -1;
+    hipPointerAttribute_t at{};
+    const bool yes = hipGetDevice(&dev) == hipSuccess && hipPointerGetAttributes(&at, ws) == hipSuccess &&
+                     at.type == hipMemoryTypeDevice && at.device == dev &&
+                     (!s || (hipStreamGetDevice(s, &of_stream) == hipSuccess && of_stream == dev));
+    (void)hipGetLastError();
+    return yes;
+}
+
+}  // namespace
+
 int gftorf_read_status(const void* ws, gftorf_status* out, void* stream) {
     if (!ws || !out) return fail(GFTORF_EINVAL, "NULL argument");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    gft::Status st;
-    hipError_t e = hipMemcpyAsync(&st, ws, sizeof(st), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return hip_fail(e, "gftorf_read_status");
+    gft::StatusReport r{};
+    hipError_t e = hipSuccess;
+    PinnedReport* pin = on_current_device(ws, s) ? take_report() : nullptr;
+    if (pin) {
+        gft::launch_status_report(ws, &pin->report, s);
+        e = hipGetLastError();
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e != hipSuccess) return hip_fail(e, "gftorf_read_status");   // pin is not given back: still written to
+        r = pin->report;
+        give_report(pin);
+    } else {   // memory of another device: the header alone is copied, then the counts
+        e = hipMemcpyAsync(&r.st, ws, sizeof(r.st), hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e != hipSuccess) return hip_fail(e, "gftorf_read_status");
+        if (r.st.magic == gft::kStatusMagic && r.st.n_items > 0 && r.st.n_items <= (1ull << 26) &&
+            r.st.wcount_off >= sizeof(gft::Status) && r.st.wcount_off % 8 == 0 && r.st.wcount_off < (1ull << 44)) {
+            std::vector<uint2> wc((size_t)r.st.n_items);
+            e = hipMemcpy(wc.data(), static_cast<const char*>(ws) + r.st.wcount_off, sizeof(uint2) * wc.size(),
+                          hipMemcpyDeviceToHost);
+            if (e != hipSuccess) return hip_fail(e, "gftorf_read_status");
+            for (const uint2& c : wc) {
+                r.n_evaluated += c.x;
+                r.n_composited += c.y;
+            }
+        }
+    }
+    const gft::Status& st = r.st;
     out->n_pairs = (int64_t)st.n_pairs;
     out->max_pairs = (int64_t)st.cap;
     out->overflow = (int32_t)st.overflow;
@@ -270,22 +339,8 @@ int gftorf_read_status(const void* ws, gftorf_status* out, void* stream) {
     out->overflow_seen = (int32_t)st.overflow_seen;
     out->sort_fault = st.magic == gft::kStatusMagic ? (int32_t)(st.sort_fault != 0u) : 0;
     out->n_pairs_seen = (int64_t)st.n_pairs_seen;
-    out->n_evaluated = out->n_composited = 0;
-    // the forward's per-work-item counts, summed here (the stream is idle)
-    if (st.magic == gft::kStatusMagic && st.n_items > 0 && st.n_items <= (1ull << 26) &&
-        st.wcount_off >= sizeof(gft::Status) && st.wcount_off % 8 == 0 && st.wcount_off < (1ull << 44)) {
-        std::vector<uint2> wc((size_t)st.n_items);
-        e = hipMemcpy(wc.data(), static_cast<const char*>(ws) + st.wcount_off, sizeof(uint2) * wc.size(),
-                      hipMemcpyDeviceToHost);
-        if (e != hipSuccess) return hip_fail(e, "gftorf_read_status");
-        unsigned long long ev = 0, co = 0;
-        for (const uint2& c : wc) {
-            ev += c.x;
-            co += c.y;
-        }
-        out->n_evaluated = (int64_t)ev;
-        out->n_composited = (int64_t)co;
-    }
+    out->n_evaluated = (int64_t)r.n_evaluated;
+    out->n_composited = (int64_t)r.n_composited;
     if (st.overflow) return fail(GFTORF_EOVERFLOW, "pairs exceeded max_pairs: " + std::to_string(st.n_pairs));
     if (out->sort_fault) return fail(GFTORF_EHIP, "depth sort: a look-back wait gave up; the forward is invalid");
     return GFTORF_OK;

@@ -85,9 +85,13 @@ struct Status {
 };
 static_assert(sizeof(Status) == 64, "the status header is the workspace's first 64 bytes");
 constexpr unsigned int kStatusMagic = 0x47465352u;
-// The (evaluations, composited) counts of every work item are summed on the
-// host by gftorf_read_status, which synchronises anyway, so no forward pays a
-// reduction launch for them.
+// The (evaluations, composited) counts of every work item are summed by
+// gftorf_read_status, which synchronises anyway, so no forward pays a reduction
+// launch for them.
+struct StatusReport {
+    Status st;
+    unsigned long long n_evaluated, n_composited;   // 0 if no forward has run
+};
 
 // Batches of few tiles split the backward's walk of a tile's list into
 // segments, so the forward keeps every pixel's transmittance at the list
@@ -250,6 +254,8 @@ inline bool one_sweep_sort(const Params&, const Workspace& w) { return w.M > 0 &
 hipError_t launch_binning(const Params& P, const Workspace& w, hipStream_t s);
 // Rectangles and tile counts in item order, from buffer 1; either may be NULL.
 void launch_item_rects(const Workspace& w, uint2* rects, uint32_t* counts, hipStream_t s);
+// Writes the report of the workspace `ws` to pinned host memory.
+void launch_status_report(const void* ws, StatusReport* host, hipStream_t s);
 void launch_tile_lists(const Params& P, const Workspace& w, hipStream_t s);   // completes every tile list
 void launch_keys_from_ranges(const Params& P, const Workspace& w, uint32_t* keys,
                              unsigned long long limit, hipStream_t s);

@@ -2,6 +2,7 @@
 image, tiles with pixels outside, and the introspection call between a forward
 and its backward."""
 import dataclasses
+import threading
 
 import numpy as np
 import pytest
@@ -227,3 +228,33 @@ def test_forward_box_test(tile, size, alpha_min):
     for k in ("rgb", "quad", "depth", "T_final"):
         assert_images_close(res[k], ref[k], ok, k)
     np.testing.assert_array_equal(res["n_contrib"][ok], ref["n_contrib"][ok])
+
+
+# the status's sums over the work items: one, and more and fewer than a round
+# of the summing workgroup, read by several threads on streams of their own
+def test_status_sums():
+    # nothing is skipped or stopped: every pixel composites every Gaussian
+    cases = [(1, 5, 3, 1), (4, 640, 260, 3), (3, 1024, 768, 1)]
+    errors = []
+
+    def work(n, W, H, F):
+        try:
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                g = scenes.draw_gaussians(n, W, H, float(W), float(W), seed=n, log_scale_mean=float(np.log(0.5)))
+                cfg = dataclasses.replace(scenes.RenderConfig(width=W, height=H, tile_w=8, tile_h=8).strict(),
+                                          alpha_max=0.5)
+                frames = scenes.identity_frames([0.0] * F, W, H, float(W), float(W), cfg.n_quad)
+                res = run_gpu(g, frames, cfg, max_pairs=1 << 20)
+                for _ in range(20):
+                    st = res["_ws"].status(stream)
+                    assert st["n_evaluated"] == st["n_composited"] == n * W * H * F
+        except BaseException as e:   # handed to the test's own thread
+            errors.append((n, W, H, F, e))
+
+    threads = [threading.Thread(target=work, args=c) for c in cases]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
