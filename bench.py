@@ -51,28 +51,28 @@ SORT_BYTES_PER_KEY_PASS = 16  # read key + value, write key + value (4 B each)
 # on: it is keyed by the workload name of the JSON line and the kernel, and
 # the sha256 of the kernel's source files must match; otherwise traffic is null.
 FETCH_SCALE, WRITE_SCALE = 1048576 / 524318, 1048576 / 1048576   # 1 GiB copy: FETCH 524318 KiB, WRITE 1048576 KiB
-COMPOSITE_FILES = ("paper_2505_05356_amd/csrc/composite.hip", "paper_2505_05356_amd/csrc/common.h")
-BIN_FILES = ("paper_2505_05356_amd/csrc/bin.hip", "paper_2505_05356_amd/csrc/common.h")
+COMPOSITE_FILES = ("paper_2505_05356_amd/csrc/composite.hip", "paper_2505_05356_amd/csrc/walk.h",
+                   "paper_2505_05356_amd/csrc/common.h")
+BIN_FILES = ("paper_2505_05356_amd/csrc/bin.hip", "paper_2505_05356_amd/csrc/walk.h",
+             "paper_2505_05356_amd/csrc/common.h")
 MLP_FILES = ("paper_2505_05356_amd/csrc/mlp.hip", "paper_2505_05356_amd/csrc/mlp.h")
-_COMPOSITE_SHA = "cd6b927c33cc7ddfef92101e8b2c3ebed96655616a2d324514a6c5f5a1bcdb0f"
-_BIN_SHA = "30381ced515e4468a2d60342f3df0e581007aa0fb0ac54ed325fcfd08fc4f716"
+_COMPOSITE_SHA = "ae76a2e9881dafca2e86c11028404d61555d7f2103fbecb8aff56b8b49d00913"
+_BIN_SHA = "a2006eed4b2428dda34c5057cc596ce2fdc24c236c9853fe831cf6c5f5cb12f3"
 # {workload: {kernel: (source files, sha256, (FETCH KiB, WRITE KiB) per launch)}};
-# k_mlp_dw counts its three launches together
+# k_mlp_dw counts its two launches together
 TRAFFIC = {
     "dynamic-200k-gaussians-8f-640x480": {
-        "k_composite_bwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (52202, 50919)),
-        "k_composite_fwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (5290, 96157)),
-        "k_tile_place": (BIN_FILES, _BIN_SHA, (9291, 154473)),
-        "k_group_place": (BIN_FILES, _BIN_SHA, (12834, 18412))},
+        "k_composite_bwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (52245, 50919)),
+        "k_composite_fwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (2508, 103292)),
+        "k_group_place": (BIN_FILES, _BIN_SHA, (12835, 18466))},
     "dynamic-1000k-1024x768-16f-2freq": {
-        "k_composite_bwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (361242, 247936)),
-        "k_composite_fwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (19686, 691885)),
-        "k_tile_place": (BIN_FILES, _BIN_SHA, (85160, 2046582)),
-        "k_group_place": (BIN_FILES, _BIN_SHA, (126590, 198364))},
+        "k_composite_bwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (361873, 247936)),
+        "k_composite_fwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (20967, 845658)),
+        "k_group_place": (BIN_FILES, _BIN_SHA, (126599, 194537))},
     "deform-mlp-200k-x8-8x256-pe10": {
-        k: (MLP_FILES, "38e594eb67121042452a36773f57beafc9891fcba0d2e72955acb9977e09c681", kib)
-        for k, kib in (("k_mlp_fwd", (214120, 7156260)), ("k_mlp_bwd", (368285, 6468750)),
-                       ("k_mlp_dw", (6575120, 275395)))},
+        k: (MLP_FILES, "fc3a13356217c024963e56c57510eb02394cc98819d7285b372b827a4d01ec1d", kib)
+        for k, kib in (("k_mlp_fwd", (34528, 7195455)), ("k_mlp_bwd", (223115, 6468895)),
+                       ("k_mlp_dw", (6673064, 275454)))},
 }
 
 
@@ -731,12 +731,6 @@ def roofline(name, avg_ms, P, E_fwd, E_bwd, C):
     if name == "k_composite_bwd":
         return alu(E_bwd * FLOP_PER_EVAL + C * BWD_FLOP_PER_COMP,
                    f"{E_bwd} evals x {FLOP_PER_EVAL} + {C} composited x {BWD_FLOP_PER_COMP}")
-    if name == "k_tile_place":
-        b = P * 4   # every (tile, Gaussian) entry written once, 4 B; its group-list reads are extra
-        a = b / t / 1e9
-        return dict(bound="hbm", achieved=round(a, 1), peak=HBM_PEAK_GBS, unit="GB/s",
-                    frac=round(a / HBM_PEAK_GBS, 4), traffic=None, kernel=name,
-                    avg_ms=round(avg_ms, 4), work=f"{b:.4g} B per launch = {P} pairs x 4 B written")
     if name == "k_sort_downsweep<pairs>":
         b = P * SORT_BYTES_PER_KEY_PASS
         a = b / t / 1e9

@@ -230,8 +230,9 @@ int gftorf_render_bwd(const gftorf_gaussians* g, const gftorf_frame* frames, int
  * sort each pass in one launch whose workgroups wait, boundedly, for the
  * digit counts of the frame's earlier sort tiles).
  * n_evaluated / n_composited are summed here from the forward's per-tile
- * counts, by one kernel on `stream` that also brings the header over (zero if no forward has filled this workspace since its first 64
- * bytes were cleared). */
+ * counts, by one kernel on `stream` that also brings the header over (zero if
+ * no forward has filled this workspace since its first 64 bytes were
+ * cleared). */
 int gftorf_read_status(const void* ws, gftorf_status* out, void* stream);
 
 /* Clears the status header of ws (its first 64 bytes: the last forward's

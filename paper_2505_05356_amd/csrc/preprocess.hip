@@ -12,9 +12,10 @@
 //
 // Layout: one thread per Gaussian; the thread loops over the frames (over some
 // of them where the Gaussians are few) so the 24 parameter floats of a
-// Gaussian are read from HBM once per batch.  Bound by its binary64
-// arithmetic, some 800 vector instructions an item (1M x 16 frames: 370 us,
-// of which the 1.2 GB that it writes take 210).
+// Gaussian are read from HBM once per batch.  Bound by each
+// item's dependent binary64 chain (some 470 vector instructions, divisions and
+// square roots among them) at three waves per SIMD: 1M x 16 frames 370 us, of
+// which the 1.2 GB that it writes would take 210.
 // Outputs are indexed by item i = frame * n + gaussian, so consecutive
 // threads write consecutive records.
 #include "common.h"
