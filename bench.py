@@ -57,22 +57,22 @@ BIN_FILES = ("paper_2505_05356_amd/csrc/bin.hip", "paper_2505_05356_amd/csrc/wal
              "paper_2505_05356_amd/csrc/common.h")
 MLP_FILES = ("paper_2505_05356_amd/csrc/mlp.hip", "paper_2505_05356_amd/csrc/mlp.h")
 _COMPOSITE_SHA = "ae76a2e9881dafca2e86c11028404d61555d7f2103fbecb8aff56b8b49d00913"
-_BIN_SHA = "a2006eed4b2428dda34c5057cc596ce2fdc24c236c9853fe831cf6c5f5cb12f3"
+_BIN_SHA = "55eef4ac0957d7893bff85ad503a5d992b2577822fd5427ed43be70cc41b2577"
 # {workload: {kernel: (source files, sha256, (FETCH KiB, WRITE KiB) per launch)}};
 # k_mlp_dw counts its two launches together
 TRAFFIC = {
     "dynamic-200k-gaussians-8f-640x480": {
-        "k_composite_bwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (52245, 50919)),
-        "k_composite_fwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (2508, 103292)),
-        "k_group_place": (BIN_FILES, _BIN_SHA, (12835, 18466))},
+        "k_composite_bwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (52236, 50919)),
+        "k_composite_fwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (2508, 103192)),
+        "k_group_place": (BIN_FILES, _BIN_SHA, (12835, 18579))},
     "dynamic-1000k-1024x768-16f-2freq": {
-        "k_composite_bwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (361873, 247936)),
-        "k_composite_fwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (20967, 845658)),
-        "k_group_place": (BIN_FILES, _BIN_SHA, (126599, 194537))},
+        "k_composite_bwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (361880, 247936)),
+        "k_composite_fwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (21344, 847981)),
+        "k_group_place": (BIN_FILES, _BIN_SHA, (126598, 195446))},
     "deform-mlp-200k-x8-8x256-pe10": {
         k: (MLP_FILES, "fc3a13356217c024963e56c57510eb02394cc98819d7285b372b827a4d01ec1d", kib)
-        for k, kib in (("k_mlp_fwd", (34528, 7195455)), ("k_mlp_bwd", (223115, 6468895)),
-                       ("k_mlp_dw", (6673064, 275454)))},
+        for k, kib in (("k_mlp_fwd", (35433, 7195836)), ("k_mlp_bwd", (223141, 6468866)),
+                       ("k_mlp_dw", (6683412, 275508)))},
 }
 
 

@@ -578,10 +578,12 @@ __global__ void k_item_rects(const uint32_t* __restrict__ dkey, const uint32_t* 
     for (long long j = (long long)blockIdx.x * blockDim.x + threadIdx.x; j < M;
          j += (long long)gridDim.x * blockDim.x) {
         const uint2 r = drect[j];
-        if (rects) rects[dval[j]] = r;
+        const uint32_t item = dval[j];
+        if (item >= M) continue;   // no forward has filled the workspace
+        if (rects) rects[item] = r;
         uint32_t xlo, xhi, ylo, yhi;
         unpack_rect(r, xlo, xhi, ylo, yhi);
-        if (counts) counts[dval[j]] = dkey[j] == kCulledKey ? 0u : (xhi - xlo + 1) * (yhi - ylo + 1);
+        if (counts) counts[item] = dkey[j] == kCulledKey ? 0u : (xhi - xlo + 1) * (yhi - ylo + 1);
     }
 }
 
