@@ -980,10 +980,10 @@ hipError_t fwd_wpt(const Params& P, const gftorf_frame* frames, const Workspace&
 // Batches of fewer tiles than this take one pixel per lane and groups of four
 // entries (more waves, and the longest chain each wave can hide), larger ones
 // two pixels per lane and groups of two (the column's terms and the staging
-// shared).  Measured: 1200 tiles 35.7 against 43.3 us, 4800 tiles 88 us both,
-// 9600 tiles 155 against 142 us.
-constexpr int64_t kFwdTiles = 4096;
-static_assert(kFwdTiles == kSplitTiles, "the split backward needs the forward's 64-entry batches and marks");
+// shared).  Measured: 1200 tiles 35.8 against 42.0 us, 2400 tiles 55.2 against
+// 54.0, 3600 tiles 74.2 against 71.6, 4800 tiles 92 against 85, 9600 tiles 167
+// against 141.
+constexpr int64_t kFwdTiles = 2048;
 
 template <int TW, int TH>
 hipError_t fwd_nf(const Params& P, const gftorf_frame* frames, const Workspace& w,

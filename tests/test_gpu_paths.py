@@ -258,3 +258,29 @@ def test_status_sums():
     for t in threads:
         t.join()
     assert not errors, errors
+
+
+# between 2048 and 4096 tiles the forward has two waves per tile and the
+# backward is split: one frame, and the same frame as often as that takes
+@pytest.mark.parametrize("tile,n_freq", [((16, 16), 1), ((16, 16), 4), ((32, 8), 2)])
+def test_two_waves_and_split_backward(tile, n_freq):
+    n, F = 500, 342
+    wl = scenes.tiny_scene(n, 37, 19, seed=n, log_scale_mean=float(np.log(0.6)))
+    wl.gaussians.opacity_logit[:] = np.random.default_rng(n).uniform(-5.2, -3.0, n).astype(np.float32)
+    cfg = dataclasses.replace(wl.cfg, tile_w=tile[0], tile_h=tile[1], T_min=0.0, freqs=(30e6, 60e6, 20e6, 50e6)[:n_freq])
+    F = F * 6 // (cfg.tiles_x * cfg.tiles_y)
+    assert 2048 <= F * cfg.tiles_x * cfg.tiles_y < 4096
+    fx = wl.frames[0].fx
+    frames = scenes.identity_frames([0.0] * F, 37, 19, fx, fx, cfg.n_quad, bg_seed=1, n_freq=n_freq)
+    frames = [frames[0]] * F
+    up1 = scenes.upstream_grads(1, cfg, seed=5)
+    one = run_gpu(wl.gaussians, frames[:1], cfg, upstream=up1)
+    res = run_gpu(wl.gaussians, frames, cfg, upstream={k: np.repeat(v, F, 0) for k, v in up1.items()})
+    ok = np.ones((1, 19, 37), bool)
+    for f in (0, F // 2, F - 1):
+        np.testing.assert_array_equal(res["n_contrib"][f], one["n_contrib"][0])
+        for k in ("rgb", "quad", "depth"):
+            assert_images_close(res[k][f:f + 1], one[k], ok, k, rtol=1e-6)
+    for k, v in one["grads"].items():
+        if v is not None:   # float32 sums of the same terms in another order
+            assert_grads_close(res["grads"][k], v.astype(np.float64) * F, k, rtol=GRAD_RTOL * 1e-2)
