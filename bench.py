@@ -56,23 +56,23 @@ COMPOSITE_FILES = ("paper_2505_05356_amd/csrc/composite.hip", "paper_2505_05356_
 BIN_FILES = ("paper_2505_05356_amd/csrc/bin.hip", "paper_2505_05356_amd/csrc/walk.h",
              "paper_2505_05356_amd/csrc/common.h")
 MLP_FILES = ("paper_2505_05356_amd/csrc/mlp.hip", "paper_2505_05356_amd/csrc/mlp.h")
-_COMPOSITE_SHA = "ae76a2e9881dafca2e86c11028404d61555d7f2103fbecb8aff56b8b49d00913"
+_COMPOSITE_SHA = "905a084cb649fb94e07ba5e5324795ef140830a44823d4a9a28089bbaf6554a4"
 _BIN_SHA = "55eef4ac0957d7893bff85ad503a5d992b2577822fd5427ed43be70cc41b2577"
 # {workload: {kernel: (source files, sha256, (FETCH KiB, WRITE KiB) per launch)}};
 # k_mlp_dw counts its two launches together
 TRAFFIC = {
     "dynamic-200k-gaussians-8f-640x480": {
         "k_composite_bwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (52236, 50919)),
-        "k_composite_fwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (2508, 103192)),
-        "k_group_place": (BIN_FILES, _BIN_SHA, (12835, 18579))},
+        "k_composite_fwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (2506, 103078)),
+        "k_group_place": (BIN_FILES, _BIN_SHA, (12835, 18535))},
     "dynamic-1000k-1024x768-16f-2freq": {
-        "k_composite_bwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (361880, 247936)),
-        "k_composite_fwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (21344, 847981)),
-        "k_group_place": (BIN_FILES, _BIN_SHA, (126598, 195446))},
+        "k_composite_bwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (361879, 247936)),
+        "k_composite_fwd": (COMPOSITE_FILES, _COMPOSITE_SHA, (21573, 847502)),
+        "k_group_place": (BIN_FILES, _BIN_SHA, (126602, 194582))},
     "deform-mlp-200k-x8-8x256-pe10": {
         k: (MLP_FILES, "fc3a13356217c024963e56c57510eb02394cc98819d7285b372b827a4d01ec1d", kib)
-        for k, kib in (("k_mlp_fwd", (35433, 7195836)), ("k_mlp_bwd", (223141, 6468866)),
-                       ("k_mlp_dw", (6683412, 275508)))},
+        for k, kib in (("k_mlp_fwd", (35996, 7196291)), ("k_mlp_bwd", (223174, 6468881)),
+                       ("k_mlp_dw", (6679515, 275557)))},
 }
 
 
